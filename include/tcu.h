@@ -140,13 +140,13 @@ int tcu_mm_tall(const void *A, int64_t n, int s, const void *B, void *C);
  * of calls of Theorem 2 (and its lower bound on right-matrix loads).
  * Reproducibility: int32 and bfloat16 results are the same on every call.
  * A binary32 result is too, unless the product splits the contracted index
- * across workgroups -- which it does when the 256 x 256 output tiles are
- * fewer than the device's compute units, or when they do not fill a whole
- * number of rounds of the persistent grid (the tiles of the last round are
- * then split) -- because the partial sums are then added into C with atomic
- * additions in no fixed order: the low bits of such a binary32 result may
- * differ from call to call (each result is within the stated summation
- * bound; the order-8192 products are not split). */
+ * across workgroups -- which it does where few output tiles with a long
+ * contracted index would leave compute units idle, or where the 256 x 256
+ * tiles do not fill a whole number of rounds of the persistent grid (the
+ * tiles of the last round are then split) -- because the partial sums are
+ * then added into C with atomic additions in no fixed order: the low bits
+ * of such a binary32 result may differ from call to call (each result is
+ * within the stated summation bound; the order-8192 products are not split). */
 int tcu_gemm(const void *A, const void *B, void *C, int64_t N);
 
 /* Stateless forms of the two calls: unit size, dtype and stream are
@@ -362,14 +362,17 @@ const char *tcu_strerror(int status);
  * choice.  Products never read the environment; only the initial value of
  * TCU_KNOB_CHECK_POINTERS comes from TCU_DEBUG at load time.
  *   TCU_KNOB_GEMM_KERNEL: TCU_PATH_AUTO, TCU_PATH_FULL_TILE (the 256 x 256
- *     persistent kernel wherever its shape conditions hold),
- *     TCU_PATH_GENERAL (the general kernel), TCU_PATH_RING (the small-tile
- *     ring kernel where its shape conditions hold).
+ *     persistent kernel wherever its whole-tile conditions hold),
+ *     TCU_PATH_GENERAL (the ring kernel filled through registers),
+ *     TCU_PATH_RING (the ring kernel's 64 x 64 tiles, filled by direct loads
+ *     where its shape conditions hold).
  *   TCU_KNOB_PP_GRID: workgroups of the persistent full-tile kernel, in the
- *     products and in the transitive closure's D updates (0: one per compute
- *     unit).
- *   TCU_KNOB_SPLIT_K: forced number of contracted-index ranges of a
- *     full-tile product with binary32/int32 output (0: by size).
+ *     products and in the transitive closure's D updates, and the number of
+ *     compute units that the choice of a product's kernel assumes (0: one
+ *     per compute unit).
+ *   TCU_KNOB_SPLIT_K: forced number of contracted-index ranges of a product
+ *     with binary32/int32 output, on the ring kernel or a forced full-tile
+ *     kernel (0: by size).
  *   TCU_KNOB_TAIL_SPLIT: forced number of ranges of the last round's tiles
  *     (0: by size; 1: none).
  *   TCU_KNOB_CHECK_POINTERS: 1 = check every operand with

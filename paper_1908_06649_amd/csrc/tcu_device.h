@@ -166,6 +166,23 @@ __device__ __forceinline__ u32x4 load_chunk(const unsigned char *p, int valid) {
   return v;
 }
 
+// 16 bytes at any byte address: one load (the memory system takes unaligned
+// vector accesses).
+__device__ __forceinline__ u32x4 load16_any(const unsigned char *p) {
+  typedef u32x4 u32x4_any __attribute__((aligned(1)));
+  return *(const u32x4_any *)p;
+}
+
+// v shifted down by `bytes` (0..15), zeros entering at the top: element e of
+// the result is element e + bytes / ES of v.
+__device__ __forceinline__ u32x4 shift_down(u32x4 v, int bytes) {
+  if (bytes & 8) v = u32x4{v[2], v[3], 0u, 0u};
+  if (bytes & 4) v = u32x4{v[1], v[2], v[3], 0u};
+  const unsigned b = 8u * (bytes & 3);
+  return u32x4{__builtin_amdgcn_alignbit(v[1], v[0], b), __builtin_amdgcn_alignbit(v[2], v[1], b),
+               __builtin_amdgcn_alignbit(v[3], v[2], b), v[3] >> b};
+}
+
 // One whole 16-byte chunk at p whose address is a multiple of kAl bytes (16,
 // 8, 4, 2 or 1): one vector load, or 16 / kAl naturally aligned narrower
 // loads.
@@ -200,10 +217,12 @@ __device__ __forceinline__ u32x4 load16(const unsigned char *p) {
 // Store 4 consecutive output values of one row of C at p (element col of
 // the row), of which the first `valid` (0..4) lie inside the matrix.  With
 // acc the stored values are read and added first (binary32 or int32 sum,
-// one rounding to the output type).  kVec: p is aligned for one vector
-// access of the 4 values.
+// one rounding to the output type).  kVec: the 4 values as one vector access
+// (p at any multiple of the element size).
 template <int DT, bool kVec, typename Acc>
 __device__ __forceinline__ void store_out4(unsigned char *p, Acc v, int valid, bool acc) {
+  typedef u32x2 u32x2_el __attribute__((aligned(2)));
+  typedef u32x4 u32x4_el __attribute__((aligned(4)));
   if constexpr (DT == TCU_I8_BOOL) {
     // 0/1 output: old OR (sum > 0); the accumulate flag is implied.  OR is
     // idempotent, so with no new flag nothing is read or written, and an
@@ -227,13 +246,13 @@ __device__ __forceinline__ void store_out4(unsigned char *p, Acc v, int valid, b
     unsigned short *q = (unsigned short *)p;
     if (kVec && valid >= 4) {
       if (acc) {
-        const u32x2 o = *(const u32x2 *)p;
+        const u32x2 o = *(const u32x2_el *)p;
         v[0] += bf16_to_f32(o[0] & 0xffffu);
         v[1] += bf16_to_f32(o[0] >> 16);
         v[2] += bf16_to_f32(o[1] & 0xffffu);
         v[3] += bf16_to_f32(o[1] >> 16);
       }
-      *(u32x2 *)p = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      *(u32x2_el *)p = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -250,13 +269,13 @@ __device__ __forceinline__ void store_out4(unsigned char *p, Acc v, int valid, b
     if (kVec && valid >= 4) {
       u32x4 w = bitcast<u32x4>(v);
       if (acc) {
-        const u32x4 o = *(const u32x4 *)p;
+        const u32x4 o = *(const u32x4_el *)p;
         if constexpr (kInt)
           w += o;
         else
           w = bitcast<u32x4>(bitcast<f32x4>(w) + bitcast<f32x4>(o));
       }
-      *(u32x4 *)p = w;
+      *(u32x4_el *)p = w;
     } else {
       unsigned *q = (unsigned *)p;
 #pragma unroll

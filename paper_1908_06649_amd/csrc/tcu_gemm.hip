@@ -793,28 +793,46 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
 }
 
 // ---------------------------------------------------------------------------
-// Small-tile kernel for 16-bit inputs (M, N multiples of 64, K a multiple of
-// one 128-byte stage): 64 x 64 output tiles, 4 waves of 32 x 32, and a ring
-// of kStages LDS stages filled by direct DMA loads kStages - 1 stages ahead.
-// Products with few tiles and a long K per tile (N = 1024: 256 tiles with
-// K = 1024 each) are latency-bound on a register-staged double buffer, which
-// exposes one L2 round trip per K step; the ring keeps kStages - 1 stages of
-// every workgroup in flight instead.
-//   * A stage of A: 64 rows x 128 bytes as four 2 KiB blocks of 16 rows,
+// Ring kernel: 128 x 128 or 64 x 64 output tiles, 4 waves (2 x 2, each a
+// quarter of the tile), any M, N, K and any row pitch.  One LDS layout serves
+// two ways of filling it:
+//   * kDma: direct 16-byte DMA loads, kStages - 1 stages ahead (16-byte row
+//     pitches, N a whole number of 16-byte chunks; a lane past the edge of C
+//     loads the last row or chunk inside instead, and a partial last stage
+//     goes through registers with zeros past K);
+//   * otherwise: 16-byte loads at any byte address into registers one stage
+//     ahead, written to the other of two LDS slots (kStages = 2).  A chunk
+//     that crosses the end of a row is loaded from the last 16 bytes inside
+//     it and shifted, and one past it repeats the last one (columns of B past
+//     N, never stored) or becomes zero (past K), without branches, so every
+//     load stays inside the operands and edge tiles cost what whole ones do.
+//     Only rows shorter than 16 bytes are loaded element by element.
+//   * A stage of A: BM rows x KB bytes as blocks of 16 rows x 64 bytes,
 //     chunk-major, so a fragment read is a linear ds_read_b128.
-//   * A stage of B: 64 k-rows x 128 bytes (64 columns), row-major, 16-byte
-//     chunks XOR-swizzled by bits 1 and 3 of the row, so that the 32 lanes
-//     of one ds_read_b64_tr_b16 pass (8 rows, 32 bytes each) hit distinct
-//     banks.
-//   * Wave w loads A block w and B rows 16w .. 16w+15 of every stage (four
-//     1 KiB DMA instructions), and computes rows 32(w/2) .., columns
-//     32(w%2) .. of the tile.
+//   * A stage of B: the stage's rows of BN columns, row-major, 16-byte chunks
+//     XOR-swizzled by the row (ring_b_swz) so that the lanes of one pass of a
+//     transposing read hit distinct banks.
+// Work items are (K range, tile) pairs: with nsplit > 1 an item sums one of
+// nsplit ranges of whole stages and adds its partial tile into C atomically
+// (binary32 and int32 outputs).
 // ---------------------------------------------------------------------------
-constexpr int kRingKB = 128;                    // bytes of K per stage
-constexpr int kRingHalf = 64 * kRingKB;         // 8 KiB per operand per stage
 
+// XOR swizzle of the 16-byte chunks of row k of a B stage whose rows hold
+// `row_bytes` (64, 128 or 256) bytes.  A pass of 32 lanes of the transposing
+// read touches rows 0-3 and 8-11 (32 bytes each, 16-bit) or rows 0-7 and
+// 16-23 (16 bytes each, int8) of a K step; the swizzle spreads the rows that
+// share a 256-byte bank window.
+template <int ES, int row_bytes>
 __device__ __forceinline__ int ring_b_swz(int k) {
-  return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+  if constexpr (ES == 2) {
+    static_assert(row_bytes == 128 || row_bytes == 256, "B stage rows");
+    if constexpr (row_bytes == 256) return ((k & 3) << 1) | (((k >> 3) & 1) << 3);
+    return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+  } else {
+    static_assert(row_bytes == 64 || row_bytes == 128, "B stage rows");
+    if constexpr (row_bytes == 128) return ((k >> 1) & 3) | (((k >> 4) & 1) << 2);
+    return ((k >> 2) & 1) | (((k >> 4) & 1) << 1);
+  }
 }
 
 // Wait until at most 4 * min(later, kMax) of this wave's DMA loads are in
@@ -831,121 +849,328 @@ __device__ __forceinline__ void ring_wait(int later) {
   }
 }
 
-template <int DT, int kStages>
-__global__ __launch_bounds__(256) void gemm_ring_kernel(
-    const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
-    unsigned char *__restrict__ C, int K, int64_t lda, int64_t ldb, int64_t ldc, int accum,
-    int tiles_m, int tiles_n) {
-  static_assert(in_bytes(DT) == 2, "16-bit inputs");
-  static_assert(kStages >= 2 && 4 * (kStages - 2) <= 63, "vmcnt range");
-  constexpr int OB = out_bytes(DT);
-  constexpr int KE = kRingKB / 2;               // contracted elements per stage
-  __shared__ __attribute__((aligned(1024))) unsigned char sA[kStages * kRingHalf];
-  __shared__ __attribute__((aligned(1024))) unsigned char sB[kStages * kRingHalf];
+template <int DT, int BM, int BN, int KB, int kStages, bool kDma>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, BM == 64 ? (kDma ? 3 : 4) : 2))) void
+gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
+                 unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
+                 int64_t ldc, int accum, int tiles_m, int tiles_n, int nsplit) {
+  constexpr bool kI8 = in_bytes(DT) == 1;
+  constexpr int ES = in_bytes(DT), OB = out_bytes(DT);
+  constexpr int EPC = 16 / ES;
+  constexpr int KE = KB / ES;                    // contracted elements per stage
+  constexpr int KK = KB / 64;                    // matrix-core K steps per stage
+  constexpr int BROW = BN * ES;                  // bytes per B row of a stage
+  constexpr int kAStage = BM * KB, kBStage = BN * KB;
+  constexpr int JA = kAStage / 4096, JB = kBStage / 4096;   // 1 KiB pieces per wave
+  constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16;
+  static_assert(!kDma || JA + JB == 4, "the stage waits count 4 DMA loads per wave");
+  static_assert(!kDma || 4 * (kStages - 2) <= 63, "vmcnt range");
+  static_assert(kDma || kStages == 2, "register-staged: two slots");
+  typedef typename std::conditional<kI8, i32x4, f32x4>::type Acc;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kStages * (kAStage + kBStage)];
+  unsigned char *const sA = smem;
+  unsigned char *const sB = smem + kStages * kAStage;
 
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int r = lane & 15, g = lane >> 4;
-  int tm, tn;
-  map_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * 64, n0 = tn * 64;
-  const int64_t lda_b = lda * 2, ldb_b = ldb * 2, ldc_b = ldc * OB;
-  const int nk = K / KE;
-
-  // DMA share of wave w (wave-uniform bases, per-lane 32-bit offsets).
-  const unsigned char *abase = A + (int64_t)(m0 + 16 * w) * lda_b;
-  const unsigned char *bbase = B + (int64_t)(16 * w) * ldb_b + (int64_t)n0 * 2;
-  unsigned aoff[2], boff[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    aoff[h] = (unsigned)((lane & 15) * lda_b) + 16u * (4 * h + (lane >> 4));
-    const int krow = 8 * h + (lane >> 3);
-    boff[h] = (unsigned)(krow * ldb_b) + 16u * ((lane & 7) ^ ring_b_swz(16 * w + krow));
+  const int tiles = tiles_m * tiles_n;
+  // Split items go K range by K range, permuted so that each XCD holds a
+  // contiguous run of them (its L2 then serves one range's panels); the
+  // items past the last multiple of 8 keep their ids.
+  int pid = blockIdx.x, slice = 0;
+  if (nsplit > 1) {
+    const int body = tiles * nsplit / 8 * 8;
+    if (pid < body) pid = (pid % 8) * (body / 8) + pid / 8;
+    slice = pid / tiles;
+    pid -= slice * tiles;
   }
-  const unsigned a_lds = lds_addr(sA) + w * 2048, b_lds = lds_addr(sB) + w * 2048;
+  int tm, tn;
+  map_tile(pid, tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int64_t lda_b = lda * ES, ldb_b = ldb * ES, ldc_b = ldc * OB;
+  const int nk_all = (K + KE - 1) / KE;
+  const int s_begin = (int)((int64_t)nk_all * slice / nsplit);
+  const int nk = (int)((int64_t)nk_all * (slice + 1) / nsplit) - s_begin;
+  const int k_first = s_begin * KE;
+
+  // Piece j of a stage of A: rows 16 (j / KK) + lane % 16, chunk 4 (j % KK) +
+  // lane / 16, at LDS bytes 1024 j + 16 lane.  Piece j of B: LDS bytes
+  // [1024 j, 1024 (j + 1)) of the row-major swizzled stage.
+  auto a_row = [&](int j) { return 16 * (j / KK) + (lane & 15); };
+  auto a_chunk = [&](int j) { return 4 * (j % KK) + (lane >> 4); };
+  auto b_row = [&](int j) { return (1024 * j + 16 * lane) / BROW; };
+  auto b_chunk = [&](int j) {
+    return (((1024 * j + 16 * lane) % BROW) / 16) ^ ring_b_swz<ES, BROW>(b_row(j));
+  };
+  // DMA: wave-uniform bases, per-lane 32-bit offsets.
+  unsigned aoff[JA], boff[JB];
+  const unsigned char *abase = A + (int64_t)m0 * lda_b + (int64_t)k_first * ES;
+  const unsigned char *bbase = B + (int64_t)k_first * ldb_b + (int64_t)n0 * ES;
+  const int c_last = (N - n0) * ES / 16 - 1;
+  if constexpr (kDma) {
+#pragma unroll
+    for (int i = 0; i < JA; ++i)
+      aoff[i] = (unsigned)(min(a_row(w * JA + i), M - 1 - m0) * lda_b) + 16u * a_chunk(w * JA + i);
+#pragma unroll
+    for (int i = 0; i < JB; ++i)
+      boff[i] = (unsigned)(b_row(w * JB + i) * ldb_b) + 16u * min(b_chunk(w * JB + i), c_last);
+  }
+  const unsigned a_lds = lds_addr(sA) + w * JA * 1024, b_lds = lds_addr(sB) + w * JB * 1024;
+  const int tail_t = K - (nk_all - 1) * KE < KE && s_begin + nk == nk_all ? nk - 1 : -1;
+  // Addresses of the register loads at stage 0, and for every piece of B the
+  // bytes its chunk is shifted by because it crosses N.
+  const bool short_rows = K < EPC || N < EPC;
+  const bool cross_n = !short_rows && n0 + BN > N && N % EPC != 0;
+  const unsigned char *pa[JA], *pb[JB];
+  int sh_b[JB];
+#pragma unroll
+  for (int i = 0; i < JA; ++i)
+    pa[i] = A + (int64_t)min(m0 + a_row(w * JA + i), M - 1) * lda_b + (int64_t)k_first * ES +
+            16 * a_chunk(w * JA + i);
+#pragma unroll
+  for (int i = 0; i < JB; ++i) {
+    const int c = n0 + b_chunk(w * JB + i) * EPC, cc = short_rows ? c : min(c, N - EPC);
+    pb[i] = B + (int64_t)(k_first + b_row(w * JB + i)) * ldb_b + (int64_t)cc * ES;
+    sh_b[i] = c < N ? (c - cc) * ES : 0;
+  }
+  auto put = [&](int slot, const u32x4 (&ra)[JA], const u32x4 (&rb)[JB]) {
+#pragma unroll
+    for (int i = 0; i < JA; ++i)
+      *(u32x4 *)(sA + slot * kAStage + (w * JA + i) * 1024 + 16 * lane) = ra[i];
+#pragma unroll
+    for (int i = 0; i < JB; ++i)
+      *(u32x4 *)(sB + slot * kBStage + (w * JB + i) * 1024 + 16 * lane) =
+          cross_n ? shift_down(rb[i], sh_b[i]) : rb[i];
+  };
+  // Stage t into registers: whole, or (tail) zeros past K.
+  auto get = [&](int t, u32x4 (&ra)[JA], u32x4 (&rb)[JB]) __attribute__((always_inline)) {
+    const int64_t at = (int64_t)t * KB, bt = (int64_t)t * KE * ldb_b;
+    if (t != tail_t && !short_rows) {
+#pragma unroll
+      for (int i = 0; i < JA; ++i) ra[i] = load16_any(pa[i] + at);
+#pragma unroll
+      for (int i = 0; i < JB; ++i) rb[i] = load16_any(pb[i] + bt);
+      return;
+    }
+    const int kleft = K - k_first - t * KE;   // contracted indices left
+    if (!short_rows) {
+#pragma unroll
+      for (int i = 0; i < JA; ++i) {
+        // the last chunk inside the row may start before this stage
+        const int c = a_chunk(w * JA + i) * EPC, back = c - min(c, kleft - EPC);
+        const u32x4 v = shift_down(load16_any(pa[i] + at - back * ES), (back * ES) & 15);
+        ra[i] = c < kleft ? v : u32x4{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int i = 0; i < JB; ++i) {
+        const int k = b_row(w * JB + i), back = k - min(k, kleft - 1);
+        rb[i] = load16_any(pb[i] + bt - back * ldb_b);
+        if (back > 0) rb[i] = u32x4{0u, 0u, 0u, 0u};
+      }
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < JA; ++i)
+      ra[i] = load_chunk<ES, false>(pa[i] + at,
+                                    max(min(kleft - a_chunk(w * JA + i) * EPC, EPC), 0));
+#pragma unroll
+    for (int i = 0; i < JB; ++i) {
+      const int nleft = N - n0 - b_chunk(w * JB + i) * EPC;
+      rb[i] = load_chunk<ES, false>(pb[i] + bt,
+                                    b_row(w * JB + i) < kleft ? max(min(nleft, EPC), 0) : 0);
+    }
+  };
   auto issue = [&](int slot, int t) {
-    const unsigned char *ga = abase + (int64_t)t * kRingKB;
+    if (t == tail_t) {
+      u32x4 ra[JA], rb[JB];
+      get(t, ra, rb);
+      put(slot, ra, rb);
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the stage waits count DMA loads
+      return;
+    }
+    const unsigned char *ga = abase + (int64_t)t * KB;
     const unsigned char *gb = bbase + (int64_t)t * KE * ldb_b;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) dma_lds16_saddr(ga, aoff[h], a_lds + slot * kRingHalf + h * 1024);
+    for (int i = 0; i < JA; ++i) dma_lds16_saddr(ga, aoff[i], a_lds + slot * kAStage + i * 1024);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) dma_lds16_saddr(gb, boff[h], b_lds + slot * kRingHalf + h * 1024);
+    for (int i = 0; i < JB; ++i) dma_lds16_saddr(gb, boff[i], b_lds + slot * kBStage + i * 1024);
   };
 
-  // Fragment offsets within a stage: A rows 32 wm .., B^T columns 32 wn ..
-  const int x_off = wm * 2 * 2048 + 16 * lane;
-  int w_off[2];
+  // Fragment offsets within a stage: A rows WTM wm .., B^T columns WTN wn ..
+  const int x_off = wm * FM * KK * 1024 + 16 * lane;
+  int w_off[FN];
 #pragma unroll
-  for (int fn = 0; fn < 2; ++fn) {
-    const int n = wn * 32 + fn * 16 + 4 * (r & 3);
-    const int k0 = 8 * g + (r >> 2);
-    w_off[fn] = k0 * kRingKB + 16 * ((n >> 3) ^ ring_b_swz(k0)) + ((2 * n) & 15);
+  for (int fn = 0; fn < FN; ++fn) {
+    const int nbase = wn * WTN + fn * 16;
+    if constexpr (!kI8) {
+      const int n = nbase + 4 * (r & 3);
+      const int k0 = 8 * g + (r >> 2);
+      w_off[fn] = k0 * BROW + 16 * ((n >> 3) ^ ring_b_swz<ES, BROW>(k0)) + ((2 * n) & 15);
+    } else {
+      const int n = nbase + 8 * (r & 1);
+      const int k0 = 16 * g + (r >> 1);
+      w_off[fn] = k0 * BROW + 16 * ((n >> 4) ^ ring_b_swz<ES, BROW>(k0)) + (n & 15);
+    }
   }
+  constexpr int kW1 = (kI8 ? 8 : 4) * BROW;      // the second half of a lane's run
+  constexpr int kWK = (kI8 ? 64 : 32) * BROW;    // the next K step
 
-  f32x4 acc[2][2];
+  Acc acc[FN][FM];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < FN; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int s0 = 0; s0 < kStages - 1; ++s0)
-    if (s0 < nk) issue(s0, s0);
-  int slot = 0;
-  for (int t = 0; t < nk; ++t) {
-    // This wave's loads of stage t done (those of the stages after it may
-    // stay in flight); the barrier makes every wave's share visible and
-    // ensures all waves finished reading stage t-1, whose slot is refilled.
-    const int later = nk - 1 - t < kStages - 2 ? nk - 1 - t : kStages - 2;
-    ring_wait<kStages - 2>(later);
-    const int refill = t + kStages - 1;
-    if (refill < nk) issue(slot == 0 ? kStages - 1 : slot - 1, refill);
-    const unsigned char *sa = sA + slot * kRingHalf;
-    const unsigned char *sb = sB + slot * kRingHalf;
+    for (int b = 0; b < FM; ++b) acc[a][b] = Acc{0, 0, 0, 0};
+  auto compute = [&](int slot) {
+    const unsigned char *sa = sA + slot * kAStage;
+    const unsigned char *sb = sB + slot * kBStage;
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      u32x4 xf[2], wf[2];
+    for (int kk = 0; kk < KK; ++kk) {
+      u32x4 xf[FM], wf[FN];
 #pragma unroll
-      for (int fm = 0; fm < 2; ++fm) xf[fm] = *(const u32x4 *)(sa + x_off + fm * 2048 + kk * 1024);
+      for (int fm = 0; fm < FM; ++fm) xf[fm] = *(const u32x4 *)(sa + x_off + (fm * KK + kk) * 1024);
 #pragma unroll
-      for (int fn = 0; fn < 2; ++fn) {
-        const u32x2 w0 = lds_read_tr16(sb + w_off[fn] + kk * 32 * kRingKB);
-        const u32x2 w1 = lds_read_tr16(sb + w_off[fn] + kk * 32 * kRingKB + 4 * kRingKB);
+      for (int fn = 0; fn < FN; ++fn) {
+        u32x2 w0, w1;
+        if constexpr (!kI8) {
+          w0 = lds_read_tr16(sb + w_off[fn] + kk * kWK);
+          w1 = lds_read_tr16(sb + w_off[fn] + kk * kWK + kW1);
+        } else {
+          w0 = lds_read_tr8(sb + w_off[fn] + kk * kWK);
+          w1 = lds_read_tr8(sb + w_off[fn] + kk * kWK + kW1);
+        }
         wf[fn] = u32x4{w0[0], w0[1], w1[0], w1[1]};
       }
 #pragma unroll
-      for (int fn = 0; fn < 2; ++fn)
+      for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
-        for (int fm = 0; fm < 2; ++fm) acc[fn][fm] = mfma_k32(DT, wf[fn], xf[fm], acc[fn][fm]);
+        for (int fm = 0; fm < FM; ++fm) {
+          if constexpr (kI8)
+            acc[fn][fm] = mfma_i8_k64(wf[fn], xf[fm], acc[fn][fm]);
+          else
+            acc[fn][fm] = mfma_k32(DT, wf[fn], xf[fm], acc[fn][fm]);
+        }
     }
-    slot = slot + 1 == kStages ? 0 : slot + 1;
+  };
+
+  if constexpr (kDma) {
+    for (int s0 = 0; s0 < kStages - 1; ++s0)
+      if (s0 < nk) issue(s0, s0);
+    int slot = 0;
+    for (int t = 0; t < nk; ++t) {
+      // This wave's loads of stage t done (those of the stages after it may
+      // stay in flight); the barrier makes every wave's share visible and
+      // ensures all waves finished reading stage t-1, whose slot is refilled.
+      const int later = nk - 1 - t < kStages - 2 ? nk - 1 - t : kStages - 2;
+      ring_wait<kStages - 2>(later);
+      const int refill = t + kStages - 1;
+      if (refill < nk) issue(slot == 0 ? kStages - 1 : slot - 1, refill);
+      compute(slot);
+      slot = slot + 1 == kStages ? 0 : slot + 1;
+    }
+  } else {
+    u32x4 ra[JA], rb[JB];
+    if (nk > 0) {
+      get(0, ra, rb);
+      put(0, ra, rb);
+    }
+    if (nk > 1) get(1, ra, rb);
+    for (int t = 0; t < nk; ++t) {
+      // Stage t is in its slot and every wave has finished reading the other
+      // one; stage t+1's loads, issued a stage ago, go there, and stage
+      // t+2's are issued before the products.
+      __syncthreads();
+      if (t + 1 < nk) put((t + 1) & 1, ra, rb);
+      if (t + 2 < nk) get(t + 2, ra, rb);
+      compute(t & 1);
+    }
   }
 
   // Epilogue: lane holds C[row][col .. col+3] of every accumulator block.
+  constexpr bool kSplittable = DT == TCU_F16_F32 || DT == TCU_BF16_F32 || DT == TCU_I8_I32;
+  if constexpr (kSplittable) {
+    if (nsplit > 1) {
+      // Partial tiles are added into C atomically, through this wave's part
+      // of LDS so that one atomic instruction covers whole runs of a row.
+      constexpr int kStride = WTN * 4 + 16;
+      constexpr int kRowsPer = 64 / WTN;         // rows per atomic instruction
+      unsigned char *stage = smem + w * 32 * kStride;
+      static_assert(4 * 32 * kStride <= kStages * (kAStage + kBStage), "staging fits the ring");
+      __syncthreads();   // every wave finished reading the ring
+      const int col = n0 + wn * WTN + lane % WTN;
 #pragma unroll
-  for (int fn = 0; fn < 2; ++fn) {
+      for (int h = 0; h < FM / 2; ++h) {
 #pragma unroll
-    for (int fm = 0; fm < 2; ++fm) {
-      const int row = m0 + wm * 32 + fm * 16 + r;
-      const int col = n0 + wn * 32 + fn * 16 + 4 * g;
-      store_out4<DT, true>(C + (int64_t)row * ldc_b + (int64_t)col * OB, acc[fn][fm], 4,
-                           accum != 0);
+        for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+          for (int fm = 0; fm < 2; ++fm)
+            *(Acc *)(stage + (fm * 16 + r) * kStride + (fn * 16 + 4 * g) * 4) =
+                acc[fn][2 * h + fm];
+        __syncthreads();
+        const int row0 = m0 + wm * WTM + 32 * h;
+#pragma unroll 8
+        for (int i = lane / WTN; i < 32; i += kRowsPer) {
+          if (row0 + i >= M || col >= N) continue;
+          unsigned char *p = C + (int64_t)(row0 + i) * ldc_b + (int64_t)col * OB;
+          const unsigned char *v = stage + i * kStride + (lane % WTN) * 4;
+          if constexpr (DT == TCU_I8_I32)
+            __hip_atomic_fetch_add((int *)p, *(const int *)v, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+          else
+            __hip_atomic_fetch_add((float *)p, *(const float *)v, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();   // reads done before the next rows overwrite
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm) {
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) {
+      const int row = m0 + wm * WTM + fm * 16 + r;
+      const int col = n0 + wn * WTN + fn * 16 + 4 * g;
+      unsigned char *p = C + (int64_t)row * ldc_b + (int64_t)col * OB;
+      const int valid = row < M ? min(max(N - col, 0), 4) : 0;
+      if (valid == 4)
+        store_out4<DT, true>(p, acc[fn][fm], 4, accum != 0);
+      else if (valid > 0)
+        store_out4<DT, false>(p, acc[fn][fm], valid, accum != 0);
     }
   }
 }
 
-// Zero the rows x row_bytes view at C (row pitch ldc_b bytes; row_bytes and
-// ldc_b multiples of 16): the starting value of a split-K product that
-// overwrites C.
-__global__ __launch_bounds__(256) void zero_fill_kernel(unsigned char *__restrict__ C, int64_t rows,
-                                                        int64_t row_bytes, int64_t ldc_b) {
-  const int64_t per_row = row_bytes / 16;
+// Zero the rows x row_words view of 4-byte words at C (row pitch ldc_w
+// words): the starting value of a split-K product that overwrites C.  With
+// kVec, row_words and ldc_w are multiples of 4.
+template <bool kVec>
+__global__ __launch_bounds__(256) void zero_fill_kernel(unsigned *__restrict__ C, int64_t rows,
+                                                        int64_t row_words, int64_t ldc_w) {
+  constexpr int V = kVec ? 4 : 1;
+  const int64_t per_row = row_words / V;
   const int64_t total = rows * per_row;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t rr = i / per_row;
-    *(u32x4 *)(C + rr * ldc_b + (i - rr * per_row) * 16) = u32x4{0u, 0u, 0u, 0u};
+    unsigned *p = C + rr * ldc_w + (i - rr * per_row) * V;
+    if constexpr (kVec)
+      *(u32x4 *)p = u32x4{0u, 0u, 0u, 0u};
+    else
+      *p = 0u;
   }
+}
+
+hipError_t zero_view(const RectArgs &a, hipStream_t stream, int num_cus) {
+  unsigned *C = (unsigned *)a.C;
+  if (a.N % 4 == 0 && a.ldc % 4 == 0)
+    hipLaunchKernelGGL(zero_fill_kernel<true>, dim3(num_cus * 4), dim3(256), 0, stream, C, a.M,
+                       a.N, a.ldc);
+  else
+    hipLaunchKernelGGL(zero_fill_kernel<false>, dim3(num_cus * 4), dim3(256), 0, stream, C, a.M,
+                       a.N, a.ldc);
+  return hipGetLastError();
 }
 
 // Zero the output tiles pid in [first, first + count) of a tiles_m x
@@ -974,25 +1199,29 @@ __global__ __launch_bounds__(256) void zero_tiles_kernel(unsigned char *__restri
 
 // The tail split: when a persistent grid of `grid` workgroups walks `tiles`
 // whole tiles and the last round holds only tiles % grid of them, most CUs
-// would idle through it.  Those tail tiles are cut into nsplit K ranges
-// instead (at least kMinStages stages each, at most grid / tail of them),
-// added into C atomically, so the last round is about 1 / nsplit as long.
-// binary32 and int32 outputs only (a bfloat16 output is rounded once from
-// the whole sum).  The test override TCU_KNOB_TAIL_SPLIT = n > 0 forces n
-// ranges (1: none).  Returns
-// nsplit (1: no tail split) and sets *full to the number of whole tiles.
+// would idle through it.  Those tail tiles are cut into K ranges instead (at
+// least kMinSplitStages stages each, at most grid / tail of them), added into
+// C atomically, so the last round is about 1 / ranges as long.
+constexpr int kMinSplitStages = 32;
+int tail_ranges(int64_t tiles, int64_t grid, int64_t stages) {
+  if (tiles <= grid || tiles % grid == 0) return 1;
+  const int64_t ns = grid / (tiles % grid), cap = stages / kMinSplitStages;
+  return (int)(ns < cap ? ns : cap);
+}
+
+// The ranges of a product's tail split (1: none), with *full set to the
+// number of whole tiles.  binary32 and int32 outputs only (a bfloat16 output
+// is rounded once from the whole sum).  The test override
+// TCU_KNOB_TAIL_SPLIT = n > 0 forces n ranges (1: none).
 template <int DT>
-int tail_split(int tiles, int grid, int64_t stages, int kMinStages, int *full) {
+int tail_split(int tiles, int grid, int64_t stages, int *full) {
   *full = tiles;
   if (DT == TCU_BF16_BF16 || tiles <= grid || tiles % grid == 0) return 1;
-  const int tail = tiles % grid;
-  int64_t ns = grid / tail;
-  const int64_t cap = stages / kMinStages;
-  if (ns > cap) ns = cap;
+  int64_t ns = tail_ranges(tiles, grid, stages);
   const int forced = knob(TCU_KNOB_TAIL_SPLIT);
   if (forced > 0) ns = forced < stages ? forced : stages;
   if (ns < 2) return 1;
-  *full = tiles - tail;
+  *full = tiles - tiles % grid;
   return (int)ns;
 }
 
@@ -1005,14 +1234,25 @@ hipError_t zero_tail(unsigned char *C, int64_t ldc_b, int tm, int tn, int full, 
   return hipGetLastError();
 }
 
-template <int DT, int BM, int BN, int WM, int WN, bool kVec, int kAl = 0>
-hipError_t launch_cfg(const RectArgs &a, hipStream_t stream) {
-  const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_kernel<DT, BM, BN, WM, WN, kVec, kAl>), dim3(tiles_m * tiles_n),
-                     dim3(64 * WM * WN), 0, stream, (const unsigned char *)a.A,
-                     (const unsigned char *)a.B, (unsigned char *)a.C, (int)a.M, (int)a.N,
-                     (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0, tiles_m, tiles_n,
-                     kNoBand, 0, kNoBand, 0);
+// The ring kernel with kTile x kTile tiles and nsplit K ranges.  A CU holds
+// two workgroups of 128 x 128 tiles (DMA: five 64-byte stages each) or three
+// of 64 x 64 (DMA: three 128-byte stages; with eight stages and one
+// workgroup per CU, order 1024 took 9.7 instead of 8.6 us and order 1120,
+// whose 324 tiles then run in two rounds, 18.6 instead of 12.2 us).
+template <int DT, int kTile, bool kDma>
+hipError_t launch_ring(const RectArgs &a, int nsplit, hipStream_t stream, int num_cus) {
+  const int tiles_m = (int)((a.M + kTile - 1) / kTile), tiles_n = (int)((a.N + kTile - 1) / kTile);
+  if (nsplit > 1 && !a.accum) {
+    const hipError_t e = zero_view(a, stream, num_cus);
+    if (e != hipSuccess) return e;
+  }
+  constexpr int KB = kDma && kTile == 128 ? 64 : 128;
+  constexpr int kStages = !kDma ? 2 : kTile == 128 ? 5 : 3;
+  hipLaunchKernelGGL((gemm_ring_kernel<DT, kTile, kTile, KB, kStages, kDma>),
+                     dim3(tiles_m * tiles_n * nsplit), dim3(256), 0, stream,
+                     (const unsigned char *)a.A, (const unsigned char *)a.B,
+                     (unsigned char *)a.C, (int)a.M, (int)a.N, (int)a.K, a.lda, a.ldb, a.ldc,
+                     a.accum ? 1 : 0, tiles_m, tiles_n, nsplit);
   return hipGetLastError();
 }
 
@@ -1048,177 +1288,234 @@ GemmPath gemm_path() {
   return GemmPath::kAuto;
 }
 
-// The general and small-tile kernels: the product on shapes the full-tile
-// kernel does not take.
+// ---------------------------------------------------------------------------
+// Choice of kernel, tile and K split: the cheapest by a model of the time
+// (microseconds) of t tiles whose contracted index is n64 pieces of 64 bytes
+// on `cus` compute units.  The constants are measured per 64-byte piece; both
+// sides at the sizes where the choice turns (us; full tile / 128 / 64):
+//   bf16 N = 1024: 30 / 15.6 / 8.6     N = 1536: - / 21.4 / 25.0
+//        N = 2048: 50 / 27.7 / 40.3    N = 2560: 64 / 57 / -
+//        N = 3072: 74 / 95 / 151       N = 4096: 108 / 167 / 332
+//   int8 N = 1536: - / 14.4 / 15.1     N = 2560: 39 / 34 / -
+//        N = 3072: 48 / 56 / 127
+// Split ranges are added atomically, after zeroing C when overwriting:
+// f16 192 x 8192 x 320 (15 tiles of 64) 37 us whole, 10.4 with 16 ranges,
+// 12.9 with 32; bf16 N = 3072 full-tile 74 whole, 135 with 2 ranges.
+// ---------------------------------------------------------------------------
+enum class Tile { kFull, k128, k64 };
+struct Choice {
+  Tile tile = Tile::k64;
+  int nsplit = 1;
+  double us = 1e30;
+};
+
+double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool splittable) {
+  switch (tile) {
+    case Tile::kFull: {
+      // one workgroup per CU, whole rounds; the last may be split
+      const double round = 0.72 * n64 + 8;
+      const int ns = splittable ? tail_ranges(t, cus, (int64_t)n64) : 1;
+      if (ns > 1) return (double)(t / cus) * round + 0.72 * n64 / ns + 12;
+      return (double)((t + cus - 1) / cus) * round;
+    }
+    case Tile::k128: {
+      // two workgroups per CU, which share its LDS bandwidth
+      const double pair = 0.65 * n64 + 5, single = 0.36 * n64 + 4;
+      const int64_t rem = t % (2 * cus);
+      const double us =
+          (double)(t / (2 * cus)) * pair + (rem > cus ? pair : rem > 0 ? single : 0.0);
+      return dma ? us : 1.1 * us;
+    }
+    default: {
+      // several workgroups per CU; below one per CU the latency of a stage
+      const double per_cu = t > cus ? (double)t / (double)cus : 1.0;
+      const double stage = 0.04 + 0.16 * per_cu;
+      return n64 * (dma || stage > 0.24 ? stage : 0.24) + 1.5 * per_cu;
+    }
+  }
+}
+
+void consider(Choice &best, Tile tile, bool dma, int64_t t, int64_t n64, int64_t cus,
+              bool splittable, double split_us, double add_us) {
+  for (int64_t ns = 1;; ns += 1 + ns / 4) {
+    // each range keeps at least 512 bytes of the contracted index
+    if (ns > 1 && (!splittable || n64 / ns < 8 || t * ns > 3 * cus)) break;
+    double us = model_us(tile, dma, t * ns, (double)((n64 + ns - 1) / ns), cus,
+                         splittable && ns == 1);
+    if (ns > 1) us += split_us + add_us * (double)ns;
+    if (us < best.us) best = Choice{tile, (int)ns, us};
+  }
+}
+
+// The ring kernel: tile and split by the model.
 template <int DT>
-hipError_t launch_general(const RectArgs &a, GemmPath path, bool vec, hipStream_t stream,
-                          int num_cus) {
+Choice choose_ring(const RectArgs &a, bool dma, bool small_only, int64_t cus) {
   constexpr int ES = in_bytes(DT);
-  const int64_t big_tiles = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-  const int64_t mid_tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128);
-  // Pitches not all multiples of 16 bytes: whole chunks of A and B (interior
-  // tiles, full K steps) in the widest naturally aligned pieces both pitches
-  // allow (8, 4, 2 or 1 bytes), edges element by element; C element by
-  // element.  128 x 128 tiles where they still give every CU a workgroup.
-  if (!vec) {
-    const int64_t pa = a.lda * ES, pb = a.ldb * ES;
-    const int al = pa % 8 == 0 && pb % 8 == 0   ? 8
-                   : pa % 4 == 0 && pb % 4 == 0 ? 4
-                   : pa % 2 == 0 && pb % 2 == 0 ? 2
-                                                : 1;
-    if (mid_tiles >= num_cus) {
-      if (al == 8) return launch_cfg<DT, 128, 128, 2, 2, false, 8>(a, stream);
-      if (al == 4) return launch_cfg<DT, 128, 128, 2, 2, false, 4>(a, stream);
-      if (ES == 2 || al == 2) return launch_cfg<DT, 128, 128, 2, 2, false, 2>(a, stream);
-      return launch_cfg<DT, 128, 128, 2, 2, false, 1>(a, stream);
-    }
-    if (al == 8) return launch_cfg<DT, 64, 64, 2, 2, false, 8>(a, stream);
-    if (al == 4) return launch_cfg<DT, 64, 64, 2, 2, false, 4>(a, stream);
-    if (ES == 2 || al == 2) return launch_cfg<DT, 64, 64, 2, 2, false, 2>(a, stream);
-    return launch_cfg<DT, 64, 64, 2, 2, false, 1>(a, stream);
+  const int64_t n64 = (a.K * ES + 63) / 64;
+  const double mn = (double)a.M * (double)a.N;
+  const double split_us = 1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), add_us = mn / 1.2e6;
+  Choice c;
+  constexpr bool kSplit = DT != TCU_BF16_BF16;
+  consider(c, Tile::k64, dma, ((a.M + 63) / 64) * ((a.N + 63) / 64), n64, cus, kSplit, split_us,
+           add_us);
+  if (!small_only)
+    consider(c, Tile::k128, dma, ((a.M + 127) / 128) * ((a.N + 127) / 128), n64, cus, kSplit,
+             split_us, add_us);
+  return c;
+}
+
+// Whether the ring kernel may fill its stages by DMA: 16-byte row pitches, N
+// a whole number of 16-byte chunks, the per-lane 32-bit offsets in range.
+template <int DT>
+bool ring_dma_ok(const RectArgs &a) {
+  constexpr int ES = in_bytes(DT);
+  return (a.lda * ES) % 16 == 0 && (a.ldb * ES) % 16 == 0 && (a.N * ES) % 16 == 0 &&
+         128 * a.lda * ES < ((int64_t)1 << 32) && 128 * a.ldb * ES < ((int64_t)1 << 32);
+}
+
+template <int DT>
+hipError_t launch_ring_choice(const RectArgs &a, bool dma, const Choice &c, hipStream_t stream,
+                              int num_cus) {
+  // Test override of the ranges (at most one per 128-byte stage).
+  int ns = c.nsplit;
+  const int forced = knob(TCU_KNOB_SPLIT_K);
+  if (forced > 0 && DT != TCU_BF16_BF16) {
+    const int64_t stages = (a.K * in_bytes(DT) + 127) / 128;
+    ns = (int)(forced < stages ? forced : stages > 1 ? stages : 1);
   }
-  // The small-tile ring kernel: 16-bit inputs, whole 64 x 64 tiles and
-  // 128-byte K stages, where the general kernel would take 64 x 64 tiles
-  // (or where forced by the test override).
-  if constexpr (ES == 2) {
-    const bool ring_ok = path != GemmPath::kGeneral && path != GemmPath::kFast &&
-                         a.M % 64 == 0 && a.N % 64 == 0 && a.K % 64 == 0 && a.K > 0 &&
-                         16 * a.lda * ES < ((int64_t)1 << 32) &&
-                         16 * a.ldb * ES < ((int64_t)1 << 32);
-    if (ring_ok && (path == GemmPath::kRing || mid_tiles < num_cus)) {
-      const int tm = (int)(a.M / 64), tn = (int)(a.N / 64);
-      hipLaunchKernelGGL((gemm_ring_kernel<DT, 8>), dim3(tm * tn), dim3(256), 0, stream,
-                         (const unsigned char *)a.A, (const unsigned char *)a.B,
-                         (unsigned char *)a.C, (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0,
-                         tm, tn);
-      return hipGetLastError();
+  if (c.tile == Tile::k128)
+    return dma ? launch_ring<DT, 128, true>(a, ns, stream, num_cus)
+               : launch_ring<DT, 128, false>(a, ns, stream, num_cus);
+  return dma ? launch_ring<DT, 64, true>(a, ns, stream, num_cus)
+             : launch_ring<DT, 64, false>(a, ns, stream, num_cus);
+}
+
+template <int DT>
+hipError_t launch_general(const RectArgs &a, GemmPath path, hipStream_t stream, int num_cus,
+                          int64_t cus) {
+  const bool dma = path != GemmPath::kGeneral && ring_dma_ok<DT>(a);
+  return launch_ring_choice<DT>(a, dma, choose_ring<DT>(a, dma, path == GemmPath::kRing, cus),
+                                stream, num_cus);
+}
+
+// The full-tile kernel on tm x tn tiles of C (all of it, or its 256-aligned
+// interior), split nsplit ways, or its last partial round split (nsplit 1).
+template <int DT, bool kEdge>
+hipError_t launch_full(const RectArgs &a, int tm, int tn, int nsplit, hipStream_t stream,
+                       int num_cus) {
+  constexpr int ES = in_bytes(DT), OB = out_bytes(DT);
+  constexpr int KE = kFastKB / ES;
+  const int tiles = tm * tn;
+  // Persistent grid: one workgroup per CU (the LDS ring admits one), each
+  // walking tiles blockIdx, blockIdx + grid, ...  The test override
+  // TCU_KNOB_PP_GRID sets the grid size instead (a tiny grid gives every
+  // workgroup many tiles).
+  const int want = knob(TCU_KNOB_PP_GRID) > 0 ? knob(TCU_KNOB_PP_GRID) : num_cus;
+  int full = 0;
+  if (nsplit > 1) {
+    if (!a.accum) {
+      const hipError_t e = zero_view(a, stream, num_cus);
+      if (e != hipSuccess) return e;
+    }
+  } else {
+    nsplit = tail_split<DT>(tiles, want < tiles ? want : tiles, (a.K + KE - 1) / KE, &full);
+    if (nsplit > 1 && !a.accum) {
+      // clipped to this launch's part of C
+      const int64_t rows = a.M < 256 * (int64_t)tm ? a.M : 256 * (int64_t)tm;
+      const int64_t cols = a.N < 256 * (int64_t)tn ? a.N : 256 * (int64_t)tn;
+      const hipError_t e = zero_tail((unsigned char *)a.C, a.ldc * OB, tm, tn, full, (int)rows,
+                                     cols * OB, stream, num_cus);
+      if (e != hipSuccess) return e;
     }
   }
-  // Otherwise the largest tiles that still give every CU a workgroup.
-  if (big_tiles >= num_cus) return launch_cfg<DT, 256, 256, 2, 2, true>(a, stream);
-  if (mid_tiles >= num_cus) return launch_cfg<DT, 128, 128, 2, 2, true>(a, stream);
-  return launch_cfg<DT, 64, 64, 2, 2, true>(a, stream);
+  const int items = full + (tiles - full) * nsplit;
+  const int grid = want < items ? want : items;
+  hipLaunchKernelGGL((gemm_pp_kernel<DT, kRingStages, kEdge>), dim3(grid), dim3(512), 0, stream,
+                     (const unsigned char *)a.A, (const unsigned char *)a.B,
+                     (unsigned char *)a.C, (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0, tm, tn,
+                     full, nsplit, (int)a.M, (int)a.N, TileRemap{}, -1);
+  return hipGetLastError();
 }
 
 template <int DT>
 hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
   constexpr int ES = in_bytes(DT), OB = out_bytes(DT);
   constexpr int KE = kFastKB / ES;
-  const bool vec = (a.lda * ES) % 16 == 0 && (a.ldb * ES) % 16 == 0 && (a.ldc * OB) % 16 == 0;
-  const int64_t big_tiles = ((a.M + 255) / 256) * ((a.N + 255) / 256);
+  constexpr bool kSplit = DT != TCU_BF16_BF16;
   const GemmPath path = gemm_path();
-  // The full-tile kernel: whole 256 x 256 tiles, whole K stages, and the
-  // per-lane 32-bit DMA offsets within a stage in range.
-  const bool fast_ok = path != GemmPath::kGeneral && vec && a.M % 256 == 0 && a.N % 256 == 0 &&
-                       a.K % KE == 0 && a.K > 0 && 256 * a.lda * ES < ((int64_t)1 << 32) &&
-                       KE * a.ldb * ES < ((int64_t)1 << 32);
-  // Split-K: when the full-tile kernel has fewer tiles than CUs and a long
-  // K, the stages are cut into nsplit ranges processed by separate work
-  // items whose partial tiles are added into C atomically (binary32 or
-  // int32 outputs only: a bfloat16 output is rounded once from the whole
-  // sum).  Each range keeps at least kMinSplitStages stages.
-  constexpr int kMinSplitStages = 32;
-  int nsplit = 1;
-  if (fast_ok && DT != TCU_BF16_BF16 && big_tiles < num_cus) {
-    const int64_t want = (num_cus + big_tiles - 1) / big_tiles;
-    const int64_t cap = (a.K / KE) / kMinSplitStages;
-    nsplit = (int)(want < cap ? want : cap);
-    if (nsplit < 1) nsplit = 1;
-  }
-  const int forced_split = knob(TCU_KNOB_SPLIT_K);   // test override of the count
-  if (forced_split > 0 && fast_ok && DT != TCU_BF16_BF16) {
-    nsplit = forced_split;
-    if (nsplit > a.K / KE) nsplit = (int)(a.K / KE);
-  }
-  if (fast_ok && (path == GemmPath::kFast || nsplit > 1 ||
-                  (path == GemmPath::kAuto && big_tiles >= num_cus))) {
-    const int tm = (int)(a.M / 256), tn = (int)(a.N / 256);
-    if (nsplit > 1 && !a.accum) {
-      hipLaunchKernelGGL(zero_fill_kernel, dim3(num_cus * 4), dim3(256), 0, stream,
-                         (unsigned char *)a.C, a.M, a.N * OB, a.ldc * OB);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    // Persistent grid: one workgroup per CU (the LDS ring admits one), each
-    // walking tiles blockIdx, blockIdx + grid, ...  The test override
-    // TCU_KNOB_PP_GRID sets the grid size instead (a tiny grid gives every
-    // workgroup many tiles).
-    const int want = knob(TCU_KNOB_PP_GRID) > 0 ? knob(TCU_KNOB_PP_GRID) : num_cus;
-    int full = 0;
-    if (nsplit == 1) {
-      const int g0 = want < tm * tn ? want : tm * tn;
-      nsplit = tail_split<DT>(tm * tn, g0, a.K / KE, kMinSplitStages, &full);
-      if (nsplit > 1 && !a.accum) {
-        const hipError_t e = zero_tail((unsigned char *)a.C, a.ldc * OB, tm, tn, full,
-                                       (int)a.M, a.N * OB, stream, num_cus);
-        if (e != hipSuccess) return e;
-      }
-    }
-    const int items = full + (tm * tn - full) * nsplit;
-    const int grid = want < items ? want : items;
-    hipLaunchKernelGGL((gemm_pp_kernel<DT, kRingStages, false>), dim3(grid), dim3(512), 0, stream,
-                       (const unsigned char *)a.A, (const unsigned char *)a.B,
-                       (unsigned char *)a.C, (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0,
-                       tm, tn, full, nsplit, (int)a.M, (int)a.N, TileRemap{}, -1);
-    return hipGetLastError();
-  }
-  // Ragged shapes (dimensions that are not multiples of the tile or of a
-  // stage, zero-padded), large enough to give every CU a 256 x 256 tile:
-  //   * N a whole number of 16-byte chunks: the full-tile kernel alone, its
-  //     edge tiles loading clamped rows and chunks and storing only inside
-  //     C, the contracted index's partial last stage zero-padded;
-  //   * otherwise the full-tile kernel takes the 256-aligned interior --
-  //     rows [0, M0) and columns [0, N0) over the whole K -- and the
-  //     general kernel the bottom rows [M0, M) (all columns) and the right
-  //     columns [N0, N) of rows [0, M0).
+  const int64_t cus = knob(TCU_KNOB_PP_GRID) > 0 ? knob(TCU_KNOB_PP_GRID) : num_cus;
+  if (path == GemmPath::kGeneral || path == GemmPath::kRing)
+    return launch_general<DT>(a, path, stream, num_cus, cus);
+  // The full-tile kernel takes 16-byte pitches (per-lane 32-bit DMA offsets
+  // in range):
+  //   * whole 256 x 256 tiles and whole K stages;
+  //   * ragged shapes with N a whole number of 16-byte chunks: its edge tiles
+  //     load clamped rows and chunks and store only inside C, the contracted
+  //     index's partial last stage is zero-padded;
+  //   * other ragged shapes: the 256-aligned interior -- rows [0, M0) and
+  //     columns [0, N0) over the whole K -- while the ring kernel takes the
+  //     bottom rows [M0, M) (all columns) and the right columns [N0, N) of
+  //     rows [0, M0).
   // Every output element is formed by one launch over the whole K, so a
-  // bfloat16 output is still rounded once.
+  // bfloat16 output is rounded once.
+  const bool vec = (a.lda * ES) % 16 == 0 && (a.ldb * ES) % 16 == 0 && (a.ldc * OB) % 16 == 0 &&
+                   256 * a.lda * ES < ((int64_t)1 << 32) && KE * a.ldb * ES < ((int64_t)1 << 32);
+  const bool whole = vec && a.M % 256 == 0 && a.N % 256 == 0 && a.K % KE == 0 && a.K > 0;
+  const int64_t n64 = (a.K + KE - 1) / KE;
+  if (path == GemmPath::kFast && whole) {
+    const int tm = (int)(a.M / 256), tn = (int)(a.N / 256);
+    // forced: the split by the override, or one range per spare CU
+    int64_t ns = kSplit && tm * tn < num_cus ? (num_cus + tm * tn - 1) / (tm * tn) : 1;
+    if (ns > n64 / kMinSplitStages) ns = n64 / kMinSplitStages > 1 ? n64 / kMinSplitStages : 1;
+    const int forced = knob(TCU_KNOB_SPLIT_K);
+    if (forced > 0 && kSplit) ns = forced < n64 ? forced : n64;
+    return launch_full<DT, false>(a, tm, tn, (int)ns, stream, num_cus);
+  }
+  const bool dma = ring_dma_ok<DT>(a);
+  Choice best = choose_ring<DT>(a, dma, false, cus);
   const int64_t M0 = a.M / 256 * 256, N0 = a.N / 256 * 256;
   const bool edges_in_kernel = (a.N * ES) % 16 == 0;
-  const int64_t tm_all = edges_in_kernel ? (a.M + 255) / 256 : M0 / 256;
-  const int64_t tn_all = edges_in_kernel ? (a.N + 255) / 256 : N0 / 256;
-  const bool ragged_ok = path == GemmPath::kAuto && vec && a.K >= KE && tm_all >= 1 &&
-                         tn_all >= 1 && tm_all * tn_all >= num_cus &&
-                         256 * a.lda * ES < ((int64_t)1 << 32) &&
-                         KE * a.ldb * ES < ((int64_t)1 << 32);
-  if (ragged_ok) {
-    const int tm = (int)tm_all, tn = (int)tn_all;
-    const int grid = num_cus < tm * tn ? num_cus : tm * tn;
-    // The tail tiles' zeroing is clipped to the kernel's part of C: all of
-    // it (N * OB is then a multiple of 16 bytes) or the 256-aligned interior.
-    int full = tm * tn;
-    const int nsplit = tail_split<DT>(tm * tn, grid, (a.K + KE - 1) / KE, kMinSplitStages, &full);
-    if (nsplit > 1 && !a.accum) {
-      hipError_t e = zero_tail((unsigned char *)a.C, a.ldc * OB, tm, tn, full,
-                               (int)(edges_in_kernel ? a.M : M0),
-                               (edges_in_kernel ? a.N : N0) * OB, stream, num_cus);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((gemm_pp_kernel<DT, kRingStages, true>), dim3(grid), dim3(512), 0, stream,
-                       (const unsigned char *)a.A, (const unsigned char *)a.B,
-                       (unsigned char *)a.C, (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0,
-                       tm, tn, full, nsplit, (int)a.M, (int)a.N, TileRemap{}, -1);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || edges_in_kernel) return e;
-    if (a.M > M0) {
-      RectArgs b = a;
-      b.A = (const unsigned char *)a.A + M0 * a.lda * ES;
-      b.C = (unsigned char *)a.C + M0 * a.ldc * OB;
+  const int64_t tm = edges_in_kernel ? (a.M + 255) / 256 : M0 / 256;
+  const int64_t tn = edges_in_kernel ? (a.N + 255) / 256 : N0 / 256;
+  if (vec && a.K >= KE && tm >= 1 && tn >= 1) {
+    Choice full;
+    const double mn = (double)a.M * (double)a.N;
+    // A split is taken on whole tiles only.
+    consider(full, Tile::kFull, true, tm * tn, n64, cus, kSplit && whole,
+             1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), mn / 1.2e6);
+    if (!edges_in_kernel) {
+      // the strips, one launch each
+      RectArgs b = a, r = a;
       b.M = a.M - M0;
-      e = launch_general<DT>(b, path, vec, stream, num_cus);
-      if (e != hipSuccess) return e;
-    }
-    if (a.N > N0) {
-      RectArgs r = a;
-      r.B = (const unsigned char *)a.B + N0 * ES;
-      r.C = (unsigned char *)a.C + N0 * OB;
       r.M = M0;
       r.N = a.N - N0;
-      e = launch_general<DT>(r, path, vec, stream, num_cus);
+      if (b.M > 0) full.us += 3 + choose_ring<DT>(b, false, false, cus).us;
+      if (r.N > 0) full.us += 3 + choose_ring<DT>(r, false, false, cus).us;
     }
-    return e;
+    if (full.us < best.us) best = full;
   }
-  return launch_general<DT>(a, path, vec, stream, num_cus);
+  if (best.tile != Tile::kFull) return launch_ring_choice<DT>(a, dma, best, stream, num_cus);
+  if (whole)
+    return launch_full<DT, false>(a, (int)tm, (int)tn, best.nsplit, stream, num_cus);
+  hipError_t e = launch_full<DT, true>(a, (int)tm, (int)tn, 1, stream, num_cus);
+  if (e != hipSuccess || edges_in_kernel) return e;
+  if (a.M > M0) {
+    RectArgs b = a;
+    b.A = (const unsigned char *)a.A + M0 * a.lda * ES;
+    b.C = (unsigned char *)a.C + M0 * a.ldc * OB;
+    b.M = a.M - M0;
+    e = launch_general<DT>(b, path, stream, num_cus, cus);
+    if (e != hipSuccess) return e;
+  }
+  if (a.N > N0) {
+    RectArgs r = a;
+    r.B = (const unsigned char *)a.B + N0 * ES;
+    r.C = (unsigned char *)a.C + N0 * OB;
+    r.M = M0;
+    r.N = a.N - N0;
+    e = launch_general<DT>(r, path, stream, num_cus, cus);
+  }
+  return e;
 }
 
 }  // namespace
