@@ -76,9 +76,9 @@ PROFILES = os.path.join(ROOT, "profiles")
 
 
 def kernel_sources(kind: str):
-    main = {"gemm": ["tcu_gemm.hip", "tcu_tc_diag.h"], "rect": ["tcu_gemm.hip", "tcu_tc_diag.h"],
+    main = {"gemm": ["tcu_gemm.hip"], "rect": ["tcu_gemm.hip"],
             "poly": ["tcu_poly.hip", "tcu_split.h"],
-            "tc": ["tcu_tc.hip", "tcu_gemm.hip", "tcu_tc_diag.h"],
+            "tc": ["tcu_tc.hip", "tcu_tc_diag.h"],
             "dft": ["tcu_dft.hip", "tcu_split.h"],
             "probe": ["tcu_probe.hip"]}.get(kind, ["tcu_tall.hip"])
     return [os.path.join(CSRC, f) for f in (*main, "tcu_device.h")]
@@ -189,9 +189,9 @@ class Workload:
             self.W = torch.empty_like(self.dA)
             return
         if self.spec["kind"] == "tc":
-            # The closure is computed in place, and its 0/1 epilogues skip the
-            # chunks whose OR changes nothing, so a call on an already closed
-            # matrix does less work: every timed call starts from the raw
+            # The closure is computed in place, and its updates skip rows that
+            # reach no pivot and words that do not change, so a call on a closed
+            # matrix does other work: every timed call starts from the raw
             # graph, restored from a pristine device copy outside the timing.
             self.A = inputs.make_tc_input(self.spec)
             self.dA = self.A.cuda()

@@ -266,8 +266,10 @@ int tcu_poly_eval_ex(const void *coef, int64_t n, const void *points, int64_t p,
  *      need not be a multiple of s.
  * The section's blocked algorithm: per pivot block, close the diagonal
  * block (A), update the pivot block row and column through it (B, C), then
- * every other block by the D function X_ij <- min(X_ij + X_ik X_kj, 1) on the
- * int8 matrix cores.  Pivot blocks here are 256 vertices wide.
+ * every other block by the D function X_ij <- min(X_ij + X_ik X_kj, 1).
+ * Pivot blocks here are 256 vertices wide, and while they are walked row i
+ * of X holds its entries as bits in its first ceil(n/128)*16 bytes (n > 256):
+ * other work must not read X until the call has finished on its stream.
  * The unit size comes from tcu_get_unit() (it sets the cost accounting);
  * the stream from tcu_get_stream().  Errors: TCU_ERR_NULL, TCU_ERR_SHAPE
  * (n out of range, ld < n, extent of 2^40 bytes or more),
@@ -366,10 +368,9 @@ const char *tcu_strerror(int status);
  *     TCU_PATH_GENERAL (the ring kernel filled through registers),
  *     TCU_PATH_RING (the ring kernel's 64 x 64 tiles, filled by direct loads
  *     where its shape conditions hold).
- *   TCU_KNOB_PP_GRID: workgroups of the persistent full-tile kernel, in the
- *     products and in the transitive closure's D updates, and the number of
- *     compute units that the choice of a product's kernel assumes (0: one
- *     per compute unit).
+ *   TCU_KNOB_PP_GRID: workgroups of the persistent full-tile kernel, and the
+ *     number of compute units that the choice of a product's kernel and the
+ *     transitive closure's division of rows assume (0: the device's).
  *   TCU_KNOB_SPLIT_K: forced number of contracted-index ranges of a product
  *     with binary32/int32 output, on the ring kernel or a forced full-tile
  *     kernel (0: by size).

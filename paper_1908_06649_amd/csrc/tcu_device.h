@@ -19,18 +19,13 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
-// Internal element-type code: int8 0/1 inputs, int8 0/1 output formed as
-// old OR (sum > 0) -- the update X <- min(X + Y Z, 1) of the transitive
-// closure's D function on 0/1 matrices.  Not part of the public tcu_dtype.
-constexpr int TCU_I8_BOOL = 16;
-
 // Input element size in bytes for a tcu_dtype.
 __host__ __device__ constexpr int in_bytes(int dt) {
-  return (dt == TCU_I8_I32 || dt == TCU_I8_BOOL) ? 1 : 2;
+  return dt == TCU_I8_I32 ? 1 : 2;
 }
 // Output element size in bytes for a tcu_dtype.
 __host__ __device__ constexpr int out_bytes(int dt) {
-  return dt == TCU_BF16_BF16 ? 2 : dt == TCU_I8_BOOL ? 1 : 4;
+  return dt == TCU_BF16_BF16 ? 2 : 4;
 }
 
 template <typename T, typename S>
@@ -173,6 +168,19 @@ __device__ __forceinline__ u32x4 load16_any(const unsigned char *p) {
   return *(const u32x4_any *)p;
 }
 
+__device__ __forceinline__ void store16_any(unsigned char *p, u32x4 v) {
+  typedef u32x4 u32x4_any __attribute__((aligned(1)));
+  *(u32x4_any *)p = v;
+}
+__device__ __forceinline__ unsigned load4_any(const unsigned char *p) {
+  typedef unsigned u32_any __attribute__((aligned(1)));
+  return *(const u32_any *)p;
+}
+__device__ __forceinline__ void store4_any(unsigned char *p, unsigned v) {
+  typedef unsigned u32_any __attribute__((aligned(1)));
+  *(u32_any *)p = v;
+}
+
 // v shifted down by `bytes` (0..15), zeros entering at the top: element e of
 // the result is element e + bytes / ES of v.
 __device__ __forceinline__ u32x4 shift_down(u32x4 v, int bytes) {
@@ -181,37 +189,6 @@ __device__ __forceinline__ u32x4 shift_down(u32x4 v, int bytes) {
   const unsigned b = 8u * (bytes & 3);
   return u32x4{__builtin_amdgcn_alignbit(v[1], v[0], b), __builtin_amdgcn_alignbit(v[2], v[1], b),
                __builtin_amdgcn_alignbit(v[3], v[2], b), v[3] >> b};
-}
-
-// One whole 16-byte chunk at p whose address is a multiple of kAl bytes (16,
-// 8, 4, 2 or 1): one vector load, or 16 / kAl naturally aligned narrower
-// loads.
-template <int kAl>
-__device__ __forceinline__ u32x4 load16(const unsigned char *p) {
-  static_assert(kAl == 16 || kAl == 8 || kAl == 4 || kAl == 2 || kAl == 1,
-                "chunk alignment 16, 8, 4, 2 or 1 bytes");
-  if constexpr (kAl == 16) {
-    return *(const u32x4 *)p;
-  } else if constexpr (kAl == 8) {
-    const u32x2 a = *(const u32x2 *)p, b = *(const u32x2 *)(p + 8);
-    return u32x4{a[0], a[1], b[0], b[1]};
-  } else if constexpr (kAl == 4) {
-    const unsigned *q = (const unsigned *)p;
-    return u32x4{q[0], q[1], q[2], q[3]};
-  } else if constexpr (kAl == 2) {
-    const unsigned short *q = (const unsigned short *)p;
-    u32x4 v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = (unsigned)q[2 * i] | ((unsigned)q[2 * i + 1] << 16);
-    return v;
-  } else {
-    u32x4 v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      v[i] = (unsigned)p[4 * i] | ((unsigned)p[4 * i + 1] << 8) | ((unsigned)p[4 * i + 2] << 16) |
-             ((unsigned)p[4 * i + 3] << 24);
-    return v;
-  }
 }
 
 // Store 4 consecutive output values of one row of C at p (element col of
@@ -223,26 +200,7 @@ template <int DT, bool kVec, typename Acc>
 __device__ __forceinline__ void store_out4(unsigned char *p, Acc v, int valid, bool acc) {
   typedef u32x2 u32x2_el __attribute__((aligned(2)));
   typedef u32x4 u32x4_el __attribute__((aligned(4)));
-  if constexpr (DT == TCU_I8_BOOL) {
-    // 0/1 output: old OR (sum > 0); the accumulate flag is implied.  OR is
-    // idempotent, so with no new flag nothing is read or written, and an
-    // unchanged word is not written back.
-    if (kVec && valid >= 4) {
-      unsigned f = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) f |= (unsigned)(v[e] > 0) << (8 * e);
-      if (f == 0u) return;
-      const unsigned old = *(const unsigned *)p;
-      unsigned w = f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w |= (unsigned)(((old >> (8 * e)) & 0xffu) != 0u) << (8 * e);
-      if (w != old) *(unsigned *)p = w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (e < valid) p[e] = (unsigned char)((p[e] != 0) | (v[e] > 0));
-    }
-  } else if constexpr (DT == TCU_BF16_BF16) {
+  if constexpr (DT == TCU_BF16_BF16) {
     unsigned short *q = (unsigned short *)p;
     if (kVec && valid >= 4) {
       if (acc) {
@@ -310,7 +268,6 @@ __device__ __forceinline__ Old4<DT> load_old4(const unsigned char *p) {
 
 template <int DT, typename Acc>
 __device__ __forceinline__ void store_sum4(unsigned char *p, Acc v, Old4<DT> o) {
-  static_assert(DT != TCU_I8_BOOL, "0/1 outputs are OR-ed, not added");
   if constexpr (DT == TCU_BF16_BF16) {
     v[0] += bf16_to_f32(o[0] & 0xffffu);
     v[1] += bf16_to_f32(o[0] >> 16);

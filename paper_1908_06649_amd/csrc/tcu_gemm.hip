@@ -13,23 +13,14 @@
 // product C_{i,j} is ever written, and each staged slab of A_i is reused
 // across all the tile's B_{i,j}.
 //
-// Data flow per K-step of 128 bytes (64 16-bit or 128 int8 elements):
-//   HBM/L2 --(16-byte loads)--> registers --> LDS (double-buffered)
-//   A rows are stored as they are (the contracted index is contiguous);
-//   B is transposed on the way (in registers, with byte permutes) so that
-//   LDS holds B^T rows -- the s x s blocks B_{i,j} in the layout the matrix
-//   core takes as its resident row operand.  LDS rows are 128 bytes with the
-//   16-byte chunks XOR-swizzled so that fragment reads and tile writes hit
-//   distinct banks.
-// Compute: 4 waves in a 2 x 2 arrangement, each owning a (BM/2) x (BN/2)
-// sub-tile of 16 x 16 accumulator blocks, fed by 16x16x32 (16-bit) or
-// 16x16x64 (int8) matrix-core instructions.  The product is formed as
-// C^T = B^T A^T so each lane holds 4 consecutive columns of one row of C,
-// stored as one 16-byte write.
+// Compute: 16 x 16 accumulator blocks fed by 16x16x32 (16-bit) or 16x16x64
+// (int8) matrix-core instructions from LDS.  The product is formed as
+// C^T = B^T A^T, the s x s blocks B_{i,j} being the matrix core's resident row
+// operand, so each lane holds 4 consecutive columns of one row of C, stored
+// as one 16-byte write.
 // Workgroup order is XCD-aware (see map_tile).
 #include "tcu_device.h"
 #include "tcu_launch.h"
-#include "tcu_tc_diag.h"
 
 namespace tcu {
 namespace {
@@ -38,11 +29,6 @@ namespace {
 // the full-tile kernel, both measured best on the order-8192 products.
 constexpr int kGroupM = 2;
 constexpr int kRingStages = 5;
-
-constexpr int kBKB = 128;  // bytes of the contracted index per K-step and LDS row
-
-
-__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row ^ (row >> 3)) & 7); }
 
 // Map a workgroup id to an output tile (tm, tn): groups of kGroupM tile
 // rows are walked column by column.  Consecutive workgroup ids are dispatched
@@ -59,229 +45,6 @@ __device__ __forceinline__ void map_tile(int pid, int tiles_m, int tiles_n, int 
   const int in_group = pid % per_group;
   tm = first_m + in_group % gsz;
   tn = in_group / gsz;
-}
-
-// C (M x N) = A (M x K) * B (K x N) [+ C when accum], operands with row
-// pitches lda, ldb, ldc (elements).  Rows, columns and contracted indices
-// beyond M, N, K are zero padding: chunks reaching past an edge are loaded
-// element by element with zeros in place of the missing elements, and only
-// in-range outputs are stored.  kVec: every pitch is a multiple of 16 bytes
-// (full chunks are vector loads, 4-value groups of C vector accesses).
-// Otherwise kAl > 0: A's and B's pitches are multiples of kAl (8, 4, 2 or 1)
-// bytes, and the whole chunks of interior tiles are loaded as 16 / kAl
-// naturally aligned pieces; kAl = 0: every chunk element by element.
-template <int DT, int BM, int BN, int WM, int WN, bool kVec, int kAl = 0>
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN, 64 * WM * WN),
-                          amdgpu_waves_per_eu(1, 1))) void
-gemm_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
-            unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
-            int64_t ldc, int accum, int tiles_m, int tiles_n, int band_tm, int skip_m,
-            int band_tn, int skip_n) {
-  constexpr bool kI8 = (in_bytes(DT) == 1);
-  constexpr int NT = 64 * WM * WN;
-  constexpr int ES = in_bytes(DT);
-  constexpr int OB = out_bytes(DT);
-  constexpr int BK = kBKB / ES;                // contracted elements per K-step
-  constexpr int EPC = 16 / ES;                 // elements per 16-byte chunk
-  constexpr int CA = BM * 8 / NT;              // A chunks per thread
-  static_assert(CA * NT == BM * 8, "A tile must split evenly over threads");
-  constexpr int NBW = BN * ES / 16;            // B 8-row blocks across the tile
-  constexpr int NBLK = (BK / 8) * NBW;         // B 8-row x 16-byte blocks per K-step
-  constexpr int CB = (NBLK + NT - 1) / NT;
-  constexpr int WTM = BM / WM, WTN = BN / WN;  // wave sub-tile
-  constexpr int FM = WTM / 16, FN = WTN / 16;
-  typedef typename std::conditional<kI8, i32x4, f32x4>::type Acc;
-
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * (BM + BN) * kBKB];
-  unsigned char *const As = smem;                  // [2][BM][128]
-  unsigned char *const Bs = smem + 2 * BM * kBKB;  // [2][BN][128]  (B^T rows)
-
-  int tm, tn;
-  map_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
-  // Tile rows from band_tm on (columns from band_tn on) start skip_m
-  // (skip_n) further: the tiles then step over a band of the output that
-  // another launch owns (the transitive closure's pivot block row/column).
-  const int m0 = tm * BM + (tm >= band_tm ? skip_m : 0);
-  const int n0 = tn * BN + (tn >= band_tn ? skip_n : 0);
-  const int64_t lda_b = lda * ES, ldb_b = ldb * ES, ldc_b = ldc * OB;  // row pitches in bytes
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wid = tid >> 6;
-  const int r = lane & 15, g = lane >> 4;
-  const int wm = wid / WN, wn = wid % WN;
-
-  Acc acc[FN][FM];
-#pragma unroll
-  for (int a = 0; a < FN; ++a)
-#pragma unroll
-    for (int b = 0; b < FM; ++b) acc[a][b] = Acc{0, 0, 0, 0};
-
-  u32x4 ra[CA];
-  u32x4 rb[CB][8];
-
-  // ---- global -> registers for the K-step starting at element k0 ----
-  // Whole tile inside M x N: only the last K-step can reach past K, and
-  // only when K is not a multiple of the step.  Interior steps load whole
-  // chunks with no per-element checks.
-  constexpr int kLd = kVec ? 16 : kAl;         // alignment of whole-chunk loads
-  const bool inside = m0 + BM <= M && n0 + BN <= N;
-  const bool interior = kLd > 0 && inside;
-  auto gload_full = [&](int k0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < CA; ++i) {
-      const int q = tid + NT * i;
-      const int row = m0 + (q >> 3), kc = k0 + (q & 7) * EPC;
-      ra[i] = load16<kLd ? kLd : 16>(A + (int64_t)row * lda_b + (int64_t)kc * ES);
-    }
-#pragma unroll
-    for (int i = 0; i < CB; ++i) {
-      const int q = tid + NT * i;
-      if (CB * NT > NBLK && q >= NBLK) break;
-      const int nb = q % NBW, kb = q / NBW;
-      const int nc = n0 + nb * EPC;
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int k = k0 + 8 * kb + rr;
-        rb[i][rr] = load16<kLd ? kLd : 16>(B + (int64_t)k * ldb_b + (int64_t)nc * ES);
-      }
-    }
-  };
-  auto gload_edge = [&](int k0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < CA; ++i) {
-      const int q = tid + NT * i;
-      const int row = m0 + (q >> 3), kc = k0 + (q & 7) * EPC;
-      const int valid = row < M ? min(max(K - kc, 0), EPC) : 0;
-      ra[i] = load_chunk<ES, kVec>(A + (int64_t)row * lda_b + (int64_t)kc * ES, valid);
-    }
-#pragma unroll
-    for (int i = 0; i < CB; ++i) {
-      const int q = tid + NT * i;
-      const int nb = q % NBW, kb = q / NBW;
-      const int nc = n0 + nb * EPC;
-      const int nvalid = q < NBLK ? min(max(N - nc, 0), EPC) : 0;
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int k = k0 + 8 * kb + rr;
-        rb[i][rr] = load_chunk<ES, kVec>(B + (int64_t)k * ldb_b + (int64_t)nc * ES,
-                                         k < K ? nvalid : 0);
-      }
-    }
-  };
-  auto gload = [&](int k0) __attribute__((always_inline)) {
-    if (interior && k0 + BK <= K)
-      gload_full(k0);
-    else
-      gload_edge(k0);
-  };
-
-  // ---- registers -> LDS buffer `buf` (B transposed on the way) ----
-  auto sstore = [&](int buf) {
-    unsigned char *as = As + buf * BM * kBKB;
-    unsigned char *bs = Bs + buf * BN * kBKB;
-#pragma unroll
-    for (int i = 0; i < CA; ++i) {
-      const int q = tid + NT * i;
-      const int row = q >> 3, c = q & 7;
-      *(u32x4 *)(as + row * kBKB + swz(row, c) * 16) = ra[i];
-    }
-#pragma unroll
-    for (int i = 0; i < CB; ++i) {
-      const int q = tid + NT * i;
-      if (q >= NBLK) break;
-      const int nb = q % NBW, kb = q / NBW;
-      if constexpr (!kI8) {
-        // 8 (k) x 8 (n) block of 16-bit values -> 8 rows of B^T, 16 bytes each
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const unsigned sel = (j & 1) ? 0x07060302u : 0x05040100u;
-          u32x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            o[e] = __builtin_amdgcn_perm(rb[i][2 * e + 1][j >> 1], rb[i][2 * e][j >> 1], sel);
-          const int row = 8 * nb + j;
-          *(u32x4 *)(bs + row * kBKB + swz(row, kb) * 16) = o;
-        }
-      } else {
-        // 8 (k) x 16 (n) block of bytes -> 16 rows of B^T, 8 bytes each
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          unsigned lo[4], hi[4];
-#pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            const unsigned x = rb[i][2 * p][d], y = rb[i][2 * p + 1][d];
-            lo[p] = __builtin_amdgcn_perm(y, x, 0x05010400u);  // n = 4d, 4d+1
-            hi[p] = __builtin_amdgcn_perm(y, x, 0x07030602u);  // n = 4d+2, 4d+3
-          }
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const unsigned *src = (t < 2) ? lo : hi;
-            const unsigned sel = (t & 1) ? 0x07060302u : 0x05040100u;
-            u32x2 o = {__builtin_amdgcn_perm(src[1], src[0], sel),
-                       __builtin_amdgcn_perm(src[3], src[2], sel)};
-            const int row = 16 * nb + 4 * d + t;
-            *(u32x2 *)(bs + row * kBKB + swz(row, kb >> 1) * 16 + (kb & 1) * 8) = o;
-          }
-        }
-      }
-    }
-  };
-
-  // ---- matrix-core work on LDS buffer `buf` ----
-  auto compute = [&](int buf) {
-    const unsigned char *as = As + buf * BM * kBKB;
-    const unsigned char *bs = Bs + buf * BN * kBKB;
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      u32x4 xf[FM];
-#pragma unroll
-      for (int fm = 0; fm < FM; ++fm) {
-        const int row = wm * WTM + 16 * fm + r;
-        xf[fm] = *(const u32x4 *)(as + row * kBKB + swz(row, kk * 4 + g) * 16);
-      }
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn) {
-        const int row = wn * WTN + 16 * fn + r;
-        const u32x4 wf = *(const u32x4 *)(bs + row * kBKB + swz(row, kk * 4 + g) * 16);
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm) {
-          if constexpr (kI8)
-            acc[fn][fm] = mfma_i8_k64(wf, xf[fm], acc[fn][fm]);
-          else
-            acc[fn][fm] = mfma_k32(DT, wf, xf[fm], acc[fn][fm]);
-        }
-      }
-    }
-  };
-
-  const int nk = (K + BK - 1) / BK;
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) gload((kt + 1) * BK);
-    compute(cur);
-    if (kt + 1 < nk) sstore(cur ^ 1);
-    __syncthreads();
-  }
-
-  // ---- epilogue: lane holds C[row][col .. col+3] of every accumulator block ----
-#pragma unroll
-  for (int fn = 0; fn < FN; ++fn) {
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm) {
-      const int row = m0 + wm * WTM + 16 * fm + r;
-      const int col = n0 + wn * WTN + 16 * fn + 4 * g;
-      unsigned char *p = C + (int64_t)row * ldc_b + (int64_t)col * OB;
-      if (kVec && inside) {
-        store_out4<DT, true>(p, acc[fn][fm], 4, accum != 0);
-      } else {
-        const int valid = row < M ? min(max(N - col, 0), 4) : 0;
-        if (valid > 0) store_out4<DT, kVec>(p, acc[fn][fm], valid, accum != 0);
-      }
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -351,7 +114,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_pe
 gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
                unsigned char *__restrict__ C, int K, int64_t lda, int64_t ldb, int64_t ldc,
                int accum, int tiles_m, int tiles_n, int full, int nsplit, int m_lim,
-               int n_lim, TileRemap remap, int diag_pid) {
+               int n_lim) {
   constexpr bool kI8 = (in_bytes(DT) == 1);
   constexpr int ES = in_bytes(DT);
   constexpr int OB = out_bytes(DT);
@@ -362,14 +125,9 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
   static_assert(kRing - 2 <= 3, "waits cover at most 3 later stages");
   typedef typename std::conditional<kI8, i32x4, f32x4>::type Acc;
 
-  // The ring (A and B parts), then, for 0/1 outputs, the epilogue's 256 x
-  // 256 flag tile in LDS of its own, so that the next tile's first stages
-  // can be loaded into the ring while the epilogue runs.
-  constexpr int kFlagBytes = DT == TCU_I8_BOOL ? 256 * 256 : 0;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kRing * kFastStage + kFlagBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kRing * kFastStage];
   unsigned char *const sA = smem;
   unsigned char *const sB = smem + kRing * kFastStage;
-  unsigned char *const sF = sB + kRing * kFastStage;
 
   // Work items: the first `full` tiles (in map_tile order) whole, then the
   // other tiles as (K slice, tile) pairs, slice-major so that the workgroups
@@ -391,14 +149,7 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = wid >> 2, q = wid & 3;
   const int r = lane & 15, g = lane >> 4;
-  // With diag_pid >= 0 (the closure's D update, which also closes the next
-  // pivot band's diagonal block -- a tile of this launch): workgroup 0 takes
-  // that tile alone and then closes the block (close_diag_block, 512
-  // threads) while the others share the remaining tiles, skipping it.
-  const bool with_diag = DT == TCU_I8_BOOL && diag_pid >= 0;
-  const int stride = with_diag ? (int)gridDim.x - 1 : (int)gridDim.x;
-  const int limit = with_diag ? total - 1 : total;
-  int item = with_diag ? (int)blockIdx.x - 1 : (int)blockIdx.x;   // -1: the diagonal tile
+  int item = (int)blockIdx.x;
   int m0, n0, nk;
   int tail_t = -1;   // item-relative index of a partial last stage, if the item holds it
   // This wave's DMA share of a stage: group 0 -> A blocks 4q..4q+3 (16 rows
@@ -447,7 +198,6 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
   bool split_item = false;   // the current item is a K slice (atomic epilogue)
   auto place = [&](int w) {
     int pid = w, slice = 0;
-    if (with_diag) pid = w < 0 ? diag_pid : (w < diag_pid ? w : w + 1);
     split_item = nsplit > 1 && w >= full;
     if (split_item) {
       int v = w - full;
@@ -457,8 +207,8 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
     }
     int tm, tn;
     map_tile(pid, tiles_m, tiles_n, tm, tn);
-    m0 = remap.m_base + tm * 256 + (tm >= remap.band_m ? remap.skip_m : 0);
-    n0 = remap.n_base + tn * 256 + (tn >= remap.band_n ? remap.skip_n : 0);
+    m0 = tm * 256;
+    n0 = tn * 256;
     const int s_begin = split_item ? (int)((int64_t)nk_all * slice / nsplit) : 0;
     nk = split_item ? (int)((int64_t)nk_all * (slice + 1) / nsplit) - s_begin : nk_all;
     if constexpr (kEdge) tail_t = (k_tail < KE && s_begin + nk == nk_all) ? nk - 1 : -1;
@@ -624,168 +374,91 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
       }
     }
 
-    bool next_issued = false;   // the next tile's first stages are already in flight
-    if constexpr (DT == TCU_I8_BOOL) {
-      // 0/1 output (a quarter of the bytes of a binary32 tile): the flags
-      // (sum > 0) go through LDS so that the read-modify-write of C is done
-      // in whole 16-byte row chunks, consecutive threads on consecutive
-      // chunks.  The flags have LDS of their own, so the next tile's first
-      // stages are issued first (the ring is free after the loop's last
-      // barrier) and load while this epilogue runs; the K loop is short here
-      // (one pivot band), so that latency would otherwise be paid per tile.
-      // Flag rows are 256 bytes with the 16-byte chunks XOR-swizzled by the
-      // row: the 16 rows one store instruction touches land in distinct
-      // banks, and a row's chunks are still one 256-byte row.
-      const int em0 = m0, en0 = n0;
-      if (item >= 0 && item + stride < limit) {
-        item += stride;
-        place(item);
-        for (int s0 = 0; s0 < kRing; ++s0)
-          if (s0 < nk) issue(s0, s0);
-        next_issued = true;
-      }
-      auto flag_at = [&](int row, int byte) {
-        return sF + row * 256 + (((byte >> 4) ^ (row & 15)) << 4) + (byte & 15);
-      };
+    // Epilogue: lane holds C[row][col .. col+3] of every accumulator block.
+    auto out_ptr = [&](int fn, int fm) {
+      const int row = m0 + grp * 128 + fm * 16 + r;
+      const int col = n0 + q * 64 + fn * 16 + 4 * g;
+      return C + (int64_t)row * ldc_b + (int64_t)col * OB;
+    };
+    // The lane's 4 columns lie wholly inside or wholly outside C (n_lim is
+    // a multiple of 4).
+    auto in_c = [&](int fn, int fm) {
+      return !kEdge ||
+             (m0 + grp * 128 + fm * 16 + r < m_lim && n0 + q * 64 + fn * 16 + 4 * g < n_lim);
+    };
+    constexpr bool kSplittable = DT == TCU_F16_F32 || DT == TCU_BF16_F32 || DT == TCU_I8_I32;
+    if (kSplittable && split_item) {
+      // Partial tiles are added into C atomically.  In the accumulator
+      // layout one atomic instruction would touch one element in each of
+      // 16 rows, so every 64-byte line gets four separate requests; the
+      // wave's 128 x 64 sub-tile goes through LDS instead (the ring is
+      // free after the loop's last barrier), 64 rows at a time, and each
+      // atomic instruction then adds 64 consecutive elements of one row.
+      // Row stride 272 bytes: the 16 rows one 16-byte store instruction
+      // touches land in distinct banks.
+      if constexpr (kSplittable) {
+        constexpr int kStride = 272;
+        unsigned char *stage = (grp == 0 ? sA : sB) + q * 64 * kStride;
+        const int col = n0 + q * 64 + lane;
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn) {
+        for (int h = 0; h < FM / 4; ++h) {
 #pragma unroll
-        for (int fm = 0; fm < FM; ++fm) {
-          const int row = grp * 128 + fm * 16 + r;
-          const int col = q * 64 + fn * 16 + 4 * g;
-          unsigned w = 0;
+          for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) w |= (unsigned)(acc[fn][fm][e] > 0) << (8 * e);
-          *(unsigned *)flag_at(row, col) = w;
+            for (int fm = 0; fm < 4; ++fm)
+              *(Acc *)(stage + (fm * 16 + r) * kStride + (fn * 16 + 4 * g) * 4) =
+                  acc[fn][h * 4 + fm];
+          __syncthreads();
+          const int row0 = m0 + grp * 128 + h * 64;
+#pragma unroll 8
+          for (int i = 0; i < 64; ++i) {
+            if (kEdge && (row0 + i >= m_lim || col >= n_lim)) continue;
+            unsigned char *p = C + (int64_t)(row0 + i) * ldc_b + (int64_t)col * OB;
+            if constexpr (DT == TCU_I8_I32)
+              __hip_atomic_fetch_add((int *)p, *(const int *)(stage + i * kStride + 4 * lane),
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+              __hip_atomic_fetch_add((float *)p, *(const float *)(stage + i * kStride + 4 * lane),
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+          __syncthreads();   // reads done before the next half (or the ring) overwrites
         }
       }
-      __syncthreads();
-      // OR is idempotent: a chunk with no new flag is neither read nor
-      // written, and a chunk whose OR changes nothing is not written back
-      // (once the closure fills in, most of a band's update is such a no-op).
-      // The flags are read first so that all of a thread's C loads are in
-      // flight together.
-      constexpr int kChunks = 256 * 16 / 512;   // 16-byte chunks per thread
-      u32x4 f[kChunks], old[kChunks];
-#pragma unroll
-      for (int j = 0; j < kChunks; ++j) {
-        const int c = threadIdx.x + 512 * j, row = c >> 4, cc = c & 15;
-        f[j] = *(const u32x4 *)flag_at(row, 16 * cc);
-      }
-#pragma unroll
-      for (int j = 0; j < kChunks; ++j) {
-        const int c = threadIdx.x + 512 * j, row = c >> 4, cc = c & 15;
-        old[j] = u32x4{0u, 0u, 0u, 0u};
-        if ((f[j][0] | f[j][1] | f[j][2] | f[j][3]) != 0u)
-          old[j] = *(const u32x4 *)(C + (int64_t)(em0 + row) * ldc_b + en0 + 16 * cc);
-      }
-#pragma unroll
-      for (int j = 0; j < kChunks; ++j) {
-        const int c = threadIdx.x + 512 * j, row = c >> 4, cc = c & 15;
-        const u32x4 nw = old[j] | f[j];
-        const u32x4 d = nw ^ old[j];
-        if ((d[0] | d[1] | d[2] | d[3]) != 0u)
-          *(u32x4 *)(C + (int64_t)(em0 + row) * ldc_b + en0 + 16 * cc) = nw;
-      }
-      __syncthreads();   // flag reads done before the next tile's epilogue rewrites them
     } else {
-      // Epilogue: lane holds C[row][col .. col+3] of every accumulator block.
-      auto out_ptr = [&](int fn, int fm) {
-        const int row = m0 + grp * 128 + fm * 16 + r;
-        const int col = n0 + q * 64 + fn * 16 + 4 * g;
-        return C + (int64_t)row * ldc_b + (int64_t)col * OB;
-      };
-      // The lane's 4 columns lie wholly inside or wholly outside C (n_lim is
-      // a multiple of 4).
-      auto in_c = [&](int fn, int fm) {
-        return !kEdge ||
-               (m0 + grp * 128 + fm * 16 + r < m_lim && n0 + q * 64 + fn * 16 + 4 * g < n_lim);
-      };
-      constexpr bool kSplittable = DT == TCU_F16_F32 || DT == TCU_BF16_F32 || DT == TCU_I8_I32;
-      if (kSplittable && split_item) {
-        // Partial tiles are added into C atomically.  In the accumulator
-        // layout one atomic instruction would touch one element in each of
-        // 16 rows, so every 64-byte line gets four separate requests; the
-        // wave's 128 x 64 sub-tile goes through LDS instead (the ring is
-        // free after the loop's last barrier), 64 rows at a time, and each
-        // atomic instruction then adds 64 consecutive elements of one row.
-        // Row stride 272 bytes: the 16 rows one 16-byte store instruction
-        // touches land in distinct banks.
-        if constexpr (kSplittable) {
-          constexpr int kStride = 272;
-          unsigned char *stage = (grp == 0 ? sA : sB) + q * 64 * kStride;
-          const int col = n0 + q * 64 + lane;
+      // Blocks fn and fn + 1 hold the two 64-byte halves of 128-byte rows
+      // of C, so they are stored back to back: a half-written line left
+      // in L2 while other stores intervene is written to memory twice
+      // (measured: 1.37x the output bytes with fn outermost, 1.006x here).
+      if (accum) {
+        // C <- C + tile: the old values of two block rows (8 blocks) are
+        // loaded together, then summed and stored -- one memory round trip
+        // per 8 blocks instead of one per block.
 #pragma unroll
-          for (int h = 0; h < FM / 4; ++h) {
+        for (int fm0 = 0; fm0 < FM; fm0 += 2) {
+          Old4<DT> old[2][FN];
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int fn = 0; fn < FN; ++fn)
+              old[j][fn] = in_c(fn, fm0 + j) ? load_old4<DT>(out_ptr(fn, fm0 + j)) : Old4<DT>{};
 #pragma unroll
-              for (int fm = 0; fm < 4; ++fm)
-                *(Acc *)(stage + (fm * 16 + r) * kStride + (fn * 16 + 4 * g) * 4) =
-                    acc[fn][h * 4 + fm];
-            __syncthreads();
-            const int row0 = m0 + grp * 128 + h * 64;
-#pragma unroll 8
-            for (int i = 0; i < 64; ++i) {
-              if (kEdge && (row0 + i >= m_lim || col >= n_lim)) continue;
-              unsigned char *p = C + (int64_t)(row0 + i) * ldc_b + (int64_t)col * OB;
-              if constexpr (DT == TCU_I8_I32)
-                __hip_atomic_fetch_add((int *)p, *(const int *)(stage + i * kStride + 4 * lane),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              else
-                __hip_atomic_fetch_add((float *)p, *(const float *)(stage + i * kStride + 4 * lane),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            __syncthreads();   // reads done before the next half (or the ring) overwrites
-          }
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+              if (in_c(fn, fm0 + j))
+                store_sum4<DT>(out_ptr(fn, fm0 + j), acc[fn][fm0 + j], old[j][fn]);
         }
       } else {
-        // Blocks fn and fn + 1 hold the two 64-byte halves of 128-byte rows
-        // of C, so they are stored back to back: a half-written line left
-        // in L2 while other stores intervene is written to memory twice
-        // (measured: 1.37x the output bytes with fn outermost, 1.006x here).
-        if (accum) {
-          // C <- C + tile: the old values of two block rows (8 blocks) are
-          // loaded together, then summed and stored -- one memory round trip
-          // per 8 blocks instead of one per block.
 #pragma unroll
-          for (int fm0 = 0; fm0 < FM; fm0 += 2) {
-            Old4<DT> old[2][FN];
+        for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int fn = 0; fn < FN; ++fn)
-                old[j][fn] = in_c(fn, fm0 + j) ? load_old4<DT>(out_ptr(fn, fm0 + j)) : Old4<DT>{};
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int fn = 0; fn < FN; ++fn)
-                if (in_c(fn, fm0 + j))
-                  store_sum4<DT>(out_ptr(fn, fm0 + j), acc[fn][fm0 + j], old[j][fn]);
-          }
-        } else {
-#pragma unroll
-          for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-            for (int fn = 0; fn < FN; ++fn)
-              if (in_c(fn, fm)) store_out4<DT, true>(out_ptr(fn, fm), acc[fn][fm], 4, false);
-        }
+          for (int fn = 0; fn < FN; ++fn)
+            if (in_c(fn, fm)) store_out4<DT, true>(out_ptr(fn, fm), acc[fn][fm], 4, false);
       }
     }
     // Every wave finished reading the ring at the last barrier of the loop.
-    if (next_issued) continue;
-    if constexpr (DT == TCU_I8_BOOL) {
-      if (with_diag && item < 0) {
-        // The block's update is stored (the epilogue ends with a workgroup
-        // barrier, which orders the stores before the loads below); the ring
-        // is free.
-        close_diag_block<true, 512>(C + (int64_t)m0 * ldc_b + n0, ldc_b, kDiagBand,
-                                    *reinterpret_cast<DiagShared *>(smem));
-        break;
-      }
-    }
-    item += stride;
-    if (item >= limit) break;
+    item += (int)gridDim.x;
+    if (item >= total) break;
     place(item);
     for (int s0 = 0; s0 < kRing; ++s0)
       if (s0 < nk) issue(s0, s0);
@@ -1256,25 +929,6 @@ hipError_t launch_ring(const RectArgs &a, int nsplit, hipStream_t stream, int nu
   return hipGetLastError();
 }
 
-// Boolean rank-Bk update of the transitive closure on 0/1 int8 data:
-// C[rows, cols] <- C OR (A[rows, 0:Bk] B[0:Bk, cols] > 0), the tile grid
-// skipping the pivot band [k0, k0 + Bk) in rows and/or columns.
-// rows_skip / cols_skip: whether the row / column range of C steps over the
-// band (then M / N is the matrix order n and the band starts at k0).
-template <int BM, int BN, bool kVec>
-hipError_t launch_bool(const unsigned char *A, const unsigned char *B, unsigned char *C,
-                       int64_t ld, int M, int N, int Bk, int k0, bool rows_skip, bool cols_skip,
-                       hipStream_t stream) {
-  const int rows = rows_skip ? M - Bk : M, cols = cols_skip ? N - Bk : N;
-  const int tiles_m = (rows + BM - 1) / BM, tiles_n = (cols + BN - 1) / BN;
-  if (tiles_m <= 0 || tiles_n <= 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_kernel<TCU_I8_BOOL, BM, BN, 2, 2, kVec>), dim3(tiles_m * tiles_n),
-                     dim3(256), 0, stream, A, B, C, M, N, Bk, ld, ld, ld, 1, tiles_m, tiles_n,
-                     rows_skip ? k0 / BM : kNoBand, rows_skip ? Bk : 0,
-                     cols_skip ? k0 / BN : kNoBand, cols_skip ? Bk : 0);
-  return hipGetLastError();
-}
-
 // Kernel selection by size; the test override TCU_KNOB_GEMM_KERNEL forces
 // the full-tile (ping-pong) kernel wherever its shape conditions hold, the
 // general kernel, or the small-tile ring kernel.
@@ -1433,7 +1087,7 @@ hipError_t launch_full(const RectArgs &a, int tm, int tn, int nsplit, hipStream_
   hipLaunchKernelGGL((gemm_pp_kernel<DT, kRingStages, kEdge>), dim3(grid), dim3(512), 0, stream,
                      (const unsigned char *)a.A, (const unsigned char *)a.B,
                      (unsigned char *)a.C, (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0, tm, tn,
-                     full, nsplit, (int)a.M, (int)a.N, TileRemap{}, -1);
+                     full, nsplit, (int)a.M, (int)a.N);
   return hipGetLastError();
 }
 
@@ -1519,80 +1173,6 @@ hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
 }
 
 }  // namespace
-
-// The transitive closure's matrix-core phases for the pivot band
-// [k0, k0 + Bk), Y = X[band, band] already closed.  Every phase is the D
-// formula X[I, J] |= X[I, band] X[band, J] over a set of tiles, computed in
-// place.  Tiles may read operand blocks that other tiles of the same launch
-// are rewriting; that is harmless because every value only grows (0 -> 1)
-// and stays between its value before the phase and the closure: with one
-// operand final (Y, or a panel finished by an earlier launch), any mix of
-// old and new values in the other gives exactly the final product.
-//   * column panel: X[I, band] |= X[I, band] Y for I outside the band;
-//   * then, in one launch, the row panel X[band, J] |= Y X[band, J] and the
-//     rest X[I, J] |= X[I, band] X[band, J]: all tiles with J outside the
-//     band (the column panel is final, so the rows I = band and I outside
-//     it take the same formula).
-hipError_t launch_tc_panels(unsigned char *X, int64_t ld, int n, int k0, int Bk,
-                            hipStream_t stream) {
-  unsigned char *band_col = X + k0;
-  const unsigned char *Y = X + (int64_t)k0 * ld + k0;
-  // Column panel tiles of 32 rows x the band: the panel's work is small and
-  // latency-bound, so twice the workgroups of 64-row tiles finish sooner
-  // (n = 8192: 9.1 -> 6.7 us per band; 32 x 128 and 64 x 128 were slower).
-  if (ld % 16 == 0)
-    return launch_bool<32, 256, true>(band_col, Y, band_col, ld, n, Bk, Bk, k0, true, false,
-                                      stream);
-  return launch_bool<32, 256, false>(band_col, Y, band_col, ld, n, Bk, Bk, k0, true, false,
-                                     stream);
-}
-
-hipError_t launch_tc_rest(unsigned char *X, int64_t ld, int n, int k0, int Bk,
-                          hipStream_t stream, int num_cus, bool close_next) {
-  const unsigned char *L = X + k0;
-  const unsigned char *R = X + (int64_t)k0 * ld;
-  // Whole 256-wide bands and 16-byte rows: the full-tile kernel over
-  // n/256 x (n/256 - 1) tiles, stepping over the band's tile column.
-  if (tc_full_tiles(n, Bk, ld)) {
-    TileRemap rm;
-    rm.band_n = k0 / 256;
-    rm.skip_n = 256;
-    const int tiles_m = n / 256, tiles_n = n / 256 - 1;
-    int diag_pid = -1;
-    if (close_next) {
-      // The next band's diagonal tile: tile row b + 1 and, the band's column
-      // b being skipped, grid column b; its index in map_tile's order.
-      const int tm = k0 / 256 + 1, tn = k0 / 256;
-      const int first_m = tm / kGroupM * kGroupM;
-      const int gsz = tiles_m - first_m < kGroupM ? tiles_m - first_m : kGroupM;
-      diag_pid = first_m * tiles_n + tn * gsz + (tm - first_m);
-    }
-    return launch_tc_tiles(X, ld, n, k0, tiles_m, tiles_n, rm, stream, num_cus, diag_pid);
-  }
-  if (ld % 16 == 0)
-    return launch_bool<128, 128, true>(L, R, X, ld, n, n, Bk, k0, false, true, stream);
-  return launch_bool<128, 128, false>(L, R, X, ld, n, n, Bk, k0, false, true, stream);
-}
-
-bool tc_full_tiles(int64_t n, int Bk, int64_t ld) {
-  return n % 256 == 0 && Bk == 256 && ld % 16 == 0 && 256 * ld < ((int64_t)1 << 32);
-}
-
-hipError_t launch_tc_tiles(unsigned char *X, int64_t ld, int n, int k0, int tiles_m,
-                           int tiles_n, const TileRemap &remap, hipStream_t stream,
-                           int num_cus, int diag_pid) {
-  // The D formula X[I, J] |= X[I, band] X[band, J] (band = [k0, k0 + 256))
-  // on a tiles_m x tiles_n grid of 256 x 256 tiles placed by remap, by at
-  // most num_cus persistent workgroups.
-  const int items = tiles_m * tiles_n;
-  if (items <= 0) return hipSuccess;
-  const int grid = num_cus < items ? num_cus : items;
-  hipLaunchKernelGGL((gemm_pp_kernel<TCU_I8_BOOL, 3, false>), dim3(grid), dim3(512), 0,
-                     stream,
-                     X + k0, X + (int64_t)k0 * ld, X, 256, ld, ld, ld, 1, tiles_m, tiles_n,
-                     tiles_m * tiles_n, 1, n, n, remap, diag_pid);
-  return hipGetLastError();
-}
 
 hipError_t launch_rect(int dtype, int s, const RectArgs &a, hipStream_t stream, int num_cus) {
   // A single contiguous strip times a single block is one native call.

@@ -1,8 +1,6 @@
 // Closure of a diagonal block of the transitive closure (Section 4.3,
-// function A on a 256-vertex pivot band), as a workgroup-wide device
-// function: the standalone one-workgroup kernel (1024 threads) and the
-// full-tile product kernel's 0/1 instance (512 threads, which closes the
-// next band's block right after updating it) share it.
+// function A on a 256-vertex pivot band), as a workgroup-wide device function
+// on rows of bits held in registers.
 #pragma once
 
 #include "tcu_device.h"
@@ -11,172 +9,113 @@ namespace tcu {
 
 constexpr int kDiagBand = 256;                  // vertices per pivot band
 constexpr int kDiagWords = kDiagBand / 32;      // 32-bit words per row
-constexpr int kTab2Pitch = 8 * 16 + 8;
+constexpr int kDiagThreads = 512;               // two threads per row
 
-// 4 bytes holding 0/1 -> 4 bits, and back.
-__device__ __forceinline__ unsigned bytes_to_bits4(unsigned x) {
-  return (x & 1u) | ((x >> 7) & 2u) | ((x >> 14) & 4u) | ((x >> 21) & 8u);
-}
-__device__ __forceinline__ unsigned bits4_to_bytes(unsigned b) {
-  return (b & 1u) | ((b & 2u) << 7) | ((b & 4u) << 14) | ((b & 8u) << 21);
+template <int kCtrl>
+__device__ __forceinline__ unsigned dpp(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, false);
 }
 
-// Value of lane h (wave-uniform) of each group of kTPR consecutive lanes
-// (kTPR 2 or 4; DPP quad permutations).
-template <int kTPR>
-__device__ __forceinline__ unsigned group_broadcast(unsigned v, int h) {
-  if constexpr (kTPR == 4) {
-    switch (h) {
-      case 0: return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x00, 0xf, 0xf, false);
-      case 1: return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x55, 0xf, 0xf, false);
-      case 2: return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xaa, 0xf, 0xf, false);
-      default: return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xff, 0xf, 0xf, false);
-    }
-  } else {
-    static_assert(kTPR == 2, "2 or 4 threads per row");
-    // quad_perm [0, 0, 2, 2] or [1, 1, 3, 3]
-    return h == 0 ? (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xa0, 0xf, 0xf, false)
-                  : (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xf5, 0xf, 0xf, false);
-  }
-}
-
-// LDS of one diagonal closure.
+// LDS of one diagonal closure: two sets, for sub-bands of even and odd index.
 struct DiagShared {
-  unsigned krow[32][kDiagWords];                 // the sub-band's published pivot rows
-  unsigned tab1[8 * 16];                         // [group][subset]
-  unsigned tab2[kDiagWords * kTab2Pitch];        // [word][group][subset]
+  u32x4 krow[2][32][2];             // the sub-band's published pivot rows
+  unsigned tab1[2][8 * 16];         // [group][subset] over T*
+  u32x4 tab2[2][8 * 16 * 2];        // over the published rows, see tab2_at
 };
+// Quad q of entry m of group g, as a u32x4 index: entry m of groups 4 j ..
+// 4 j + 3 share a 128-byte window, 32 bytes each.
+__device__ __forceinline__ int tab2_at(int g, int m, int q) {
+  return 8 * (16 * (g >> 2) + m) + 2 * (g & 3) + q;
+}
 
-// Close the Bk x Bk diagonal block at D (row pitch ld; entries already 0/1),
-// Bk <= 256, with the kThreads threads of the workgroup (512 or 1024; every
-// thread must call it: it synchronises the workgroup).  Row i is held as 8
-// words of bits by the kThreads / 256 threads of row i (8 / that many words
-// each).  The pivots are taken in sub-bands K of 32; for each:
+// Close the Bk x Bk block, Bk <= 256, whose rows the workgroup's 512 threads
+// (every one must call it: it synchronises the workgroup) hold as bits: row i
+// is 8 words (bit b of word w = column 32 w + b; zero past Bk, as are the rows
+// past Bk), words 0-3 in thread 2 i and 4-7 in thread 2 i + 1.  The pivots are
+// taken in sub-bands K of 32, the rows of wave K; for each:
 //   * the pivots' current rows are published to LDS;
-//   * one wave closes the 32 x 32 block of K's rows and columns (the
-//     iterative algorithm on 32 one-word rows, the pivot row broadcast with
-//     readlane), giving T*[k]: the pivots reachable from pivot k through K,
-//     k included;
+//   * wave K closes the 32 x 32 block of K's rows and columns (the iterative
+//     algorithm on 32 one-word rows, the pivot row broadcast with readlane),
+//     giving T*[k]: the pivots reachable from pivot k through K, k included;
 //   * every row i (pivot or not) forms R_i, the union of T*[k] over the
 //     pivots k it has an edge to, and ORs in the published rows of R_i.
 // That is the iterative algorithm's 32 steps over K: a vertex reaches v
 // through K exactly when some pivot it reaches through K has an edge to v.
 // Both unions over a 32-bit set are taken 4 bits at a time from tables of
 // all 16 unions of 4 consecutive pivots' words (8 lookups instead of 32
-// masked terms): tab1 over T*, tab2 over each word of the published rows.
-// Regions of tab2 kTab2Pitch = 136 words apart start 8 banks further on per
-// word, so the lookups of the words a wave touches at once fall on distinct
-// bank windows (16 subsets of one region lie in 16 distinct banks).
-template <bool kVec, int kThreads>
-__device__ __forceinline__ void close_diag_block(unsigned char *D, int64_t ld, int Bk,
-                                                 DiagShared &s) {
-  constexpr int kTPR = kThreads / kDiagBand;     // threads per row
-  constexpr int kWPT = kDiagWords / kTPR;        // words per thread
-  const int t = threadIdx.x;
-  const int i = t / kTPR;                        // row
-  const int w0 = kWPT * (t % kTPR);              // this thread's words w0 .. w0 + kWPT - 1
-  unsigned row[kWPT];
-  // bytes -> bits (bit b of word w = column 32w + b)
-  const unsigned char *src = D + (int64_t)i * ld;
-#pragma unroll
-  for (int q = 0; q < kWPT; ++q) {
-    const int w = w0 + q;
-    unsigned word = 0;
-    if (i < Bk) {
-      if (kVec && 32 * w + 32 <= Bk) {
-        const u32x4 a = *(const u32x4 *)(src + 32 * w);
-        const u32x4 b = *(const u32x4 *)(src + 32 * w + 16);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          word |= bytes_to_bits4(a[c]) << (4 * c);
-          word |= bytes_to_bits4(b[c]) << (16 + 4 * c);
-        }
-      } else {
-        for (int b = 0; b < 32; ++b)
-          if (32 * w + b < Bk && src[32 * w + b]) word |= 1u << b;
-      }
-    }
-    row[q] = word;
-  }
+// masked terms): tab1 over T*, built by wave K, and tab2 over the published
+// rows, built by the others meanwhile.  The eight lanes of one pass of a
+// 16-byte lookup are four rows; row p of them takes groups p, p + 1, .. (mod
+// 4), so that the four read distinct bank windows whatever their subsets.
+// The sub-bands alternate between two sets of tables: two barriers each.  The
+// chain of eight sub-bands sets the time: 8.5 us with tables of single words
+// (32 lookups per thread), three barriers and wave 0 closing every block.
+__device__ __forceinline__ void close_diag_rows(unsigned (&row)[4], int Bk, DiagShared &s) {
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int q = t & 1, p = (t >> 1) & 3;        // this thread's quad; its row mod 4
 #pragma unroll
   for (int sb = 0; sb < kDiagWords; ++sb) {
     if (32 * sb >= Bk) break;
-    const int nk = Bk - 32 * sb < 32 ? Bk - 32 * sb : 32;   // pivots in this sub-band
-    const unsigned kmask = nk == 32 ? ~0u : (1u << nk) - 1u;
-    if (i >= 32 * sb && i < 32 * sb + 32) {
-#pragma unroll
-      for (int q = 0; q < kWPT; ++q) s.krow[i - 32 * sb][w0 + q] = row[q];
-    }
+    const int buf = sb & 1;
+    if (wave == sb) s.krow[buf][lane >> 1][q] = u32x4{row[0], row[1], row[2], row[3]};
     __syncthreads();
-    // (Pivots past nk have zero rows and no bits in kmask: they add nothing.)
-    if (t < 64) {
-      // wave 0: lanes 0..31 close the pivot block; then tab1 from T*.
-      unsigned tk = t < 32 ? s.krow[t][sb] & kmask : 0u;
+    // word sb of this thread's row, in both its lanes (quad permutations
+    // [0, 0, 2, 2] and [1, 1, 3, 3])
+    const unsigned edges = sb < 4 ? dpp<0xa0>(row[sb & 3]) : dpp<0xf5>(row[sb & 3]);
+    if (wave == sb) {
+      unsigned tk = edges;
 #pragma unroll
       for (int kk = 0; kk < 32; ++kk) {
-        const unsigned pivot = (unsigned)__builtin_amdgcn_readlane((int)tk, kk);
+        const unsigned pivot = (unsigned)__builtin_amdgcn_readlane((int)tk, 2 * kk);
         tk |= pivot & (0u - ((tk >> kk) & 1u));
       }
-      const unsigned tstar = t < 32 ? (tk | (1u << t)) : 0u;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = t + 64 * h, grp = e >> 4, m = e & 15;
-        unsigned v = 0;
+      tk |= 1u << (lane >> 1);
+      // tab1: lanes 8 g .. 8 g + 7 hold pivots 4 g .. 4 g + 3 twice; lane
+      // 8 g + l builds subsets 2 l and 2 l + 1.
+      const unsigned mine0 = dpp<0x00>(tk), mine1 = dpp<0xaa>(tk);   // its quad's two pivots
+      const unsigned far0 = dpp<0x141>(mine0), far1 = dpp<0x141>(mine1);   // the other quad's
+      const bool upper = lane & 4;
+      const unsigned v0 = upper ? far0 : mine0, v1 = upper ? far1 : mine1;
+      const unsigned v2 = upper ? mine0 : far0, v3 = upper ? mine1 : far1;
+      unsigned e = 0;                                  // subset 2 (lane % 8)
+      if (lane & 1) e |= v1;
+      if (lane & 2) e |= v2;
+      if (lane & 4) e |= v3;
+      unsigned *t1 = s.tab1[buf] + 2 * lane;
+      t1[0] = e;
+      t1[1] = e | v0;
+    } else {
+      // tab2: 256 quads (subset m of group g, quad q) by the seven others
+      const int idx = 64 * (wave < sb ? wave : wave - 1) + lane;
+      if (idx < 256) {
+        const int g = idx >> 5, m = (idx >> 1) & 15, qq = idx & 1;
+        u32x4 e = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-          const unsigned x = (unsigned)__shfl((int)tstar, 4 * grp + b, 64);
-          v |= x & (0u - ((unsigned)(m >> b) & 1u));
+          const u32x4 v = s.krow[buf][4 * g + b][qq];
+          const unsigned mask = 0u - ((unsigned)(m >> b) & 1u);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) e[c] |= v[c] & mask;
         }
-        s.tab1[e] = v;
+        s.tab2[buf][tab2_at(g, m, qq)] = e;
       }
-    }
-    // tab2[w][grp][m] = union of word w of the published rows 4 grp + b, b in m
-#pragma unroll
-    for (int e0 = 0; e0 < kDiagWords * 128; e0 += kThreads) {
-      const int e = e0 + t;
-      const int w = e >> 7, grp = (e >> 4) & 7, m = e & 15;
-      unsigned v = 0;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) v |= s.krow[4 * grp + b][w] & (0u - ((unsigned)(m >> b) & 1u));
-      s.tab2[w * kTab2Pitch + (e & 127)] = v;
     }
     __syncthreads();
-    // word sb of row i, from the thread of the row that holds it
-    const unsigned wsb = group_broadcast<kTPR>(row[sb % kWPT], sb / kWPT);
-    const unsigned edges = wsb & kmask;
-    unsigned reach = 0;
+    if (__any(edges != 0u)) {
+      unsigned reach = 0;
 #pragma unroll
-    for (int grp = 0; grp < 8; ++grp) reach |= s.tab1[16 * grp + ((edges >> (4 * grp)) & 15u)];
-    reach &= kmask;
+      for (int g = 0; g < 8; ++g) reach |= s.tab1[buf][16 * g + ((edges >> (4 * g)) & 15u)];
+      u32x4 add = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int q = 0; q < kWPT; ++q) {
-      const unsigned *t2 = s.tab2 + kTab2Pitch * (w0 + q);
-      unsigned add = 0;
-#pragma unroll
-      for (int grp = 0; grp < 8; ++grp) add |= t2[16 * grp + ((reach >> (4 * grp)) & 15u)];
-      row[q] |= add;
-    }
-    __syncthreads();   // krow and the tables are rewritten by the next sub-band
-  }
-  // bits -> bytes
-  if (i < Bk) {
-    unsigned char *dst = D + (int64_t)i * ld;
-#pragma unroll
-    for (int q = 0; q < kWPT; ++q) {
-      const int w = w0 + q;
-      if (kVec && 32 * w + 32 <= Bk) {
-        u32x4 a, b;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          a[c] = bits4_to_bytes(row[q] >> (4 * c));
-          b[c] = bits4_to_bytes(row[q] >> (16 + 4 * c));
-        }
-        *(u32x4 *)(dst + 32 * w) = a;
-        *(u32x4 *)(dst + 32 * w + 16) = b;
-      } else {
-        for (int b = 0; b < 32; ++b)
-          if (32 * w + b < Bk) dst[32 * w + b] = (unsigned char)((row[q] >> b) & 1u);
+      for (int j = 0; j < 4; ++j) {
+        const int w = (j + p) & 3;                     // groups w and 4 + w
+        const unsigned bits = reach >> (4 * w);
+        add |= s.tab2[buf][tab2_at(w, (int)(bits & 15u), q)];
+        add |= s.tab2[buf][tab2_at(4 + w, (int)((bits >> 16) & 15u), q)];
       }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) row[c] |= add[c];
     }
   }
 }
