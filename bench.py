@@ -124,11 +124,11 @@ def dft_levels(n: int, s: int) -> int:
 
 
 def dft_launches(n: int, s: int) -> int:
-    """Launches of tcu_dft for length n with the library's default choice:
-    two consecutive full-radix levels in one launch where it pairs them (level
-    t+1 of full radix, and P_t >= 16 or P_t = 1 with at least 16 groups per
-    vector), else one launch per level.  Each launch reads and writes the
-    array once."""
+    """Launches of tcu_dft for a vector too long to be transformed whole in LDS
+    (n > 2^13; shorter ones take one): two consecutive full-radix levels in
+    one launch where the library pairs them (level t+1 of full radix, and
+    P_t >= 16 or P_t = 1 with at least 16 groups per vector), else one
+    launch per level.  Each launch reads and writes the array once."""
     levels, P, t, launches = dft_levels(n, s), 1, 1, 0
     while t <= levels:
         n2 = n // P // s

@@ -293,9 +293,9 @@ int tcu_transitive_closure_ex(void *X, int64_t n, int64_t ld, int s, void *hip_s
  *   x: batch * n complex values, each two binary32 (re, im), vector b at
  *      x + 2 b n floats; read only.
  *   y: batch * n complex values, written; must not overlap x or work.
- *   work: batch * n complex values of scratch the levels alternate through
- *      (its contents are overwritten); must not overlap x or y; may be NULL
- *      when n <= s (one level).
+ *   work: batch * n complex values of scratch the levels may alternate through
+ *      (its contents are then overwritten); must not overlap x or y; may be
+ *      NULL when n <= s (one level).
  *   n: a power of two, 1 <= n <= TCU_MAX_DFT_N; batch >= 0 (0: no-op).
  * The unit size and stream come from tcu_get_unit() / tcu_get_stream().
  * Errors: TCU_ERR_NULL, TCU_ERR_SHAPE (n not a power of two or out of range,
@@ -378,9 +378,9 @@ const char *tcu_strerror(int status);
  *     (0: by size; 1: none).
  *   TCU_KNOB_CHECK_POINTERS: 1 = check every operand with
  *     tcu_check_device_range before launching, 0 = no checks.
- *   TCU_KNOB_DFT_PAIRS: 1 = every DFT level its own launch; 0 = two
- *     consecutive full-radix levels in one launch where possible (the same
- *     result, bit for bit).
+ *   TCU_KNOB_DFT_PAIRS: 1 = every DFT level its own launch; 0 = all levels of
+ *     a short vector, or two consecutive full-radix levels, in one launch
+ *     where possible (the same result, bit for bit).
  * Returns TCU_OK, or TCU_ERR_UNSUPPORTED for an unknown knob or a value
  * out of range (the knob is then unchanged); tcu_get_knob returns -1 for an
  * unknown knob.  Changing a knob while another thread issues calls is safe
