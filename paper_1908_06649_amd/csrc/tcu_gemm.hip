@@ -480,8 +480,13 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
 //     N, never stored) or becomes zero (past K), without branches, so every
 //     load stays inside the operands and edge tiles cost what whole ones do.
 //     Only rows shorter than 16 bytes are loaded element by element.
-//   * A stage of A: BM rows x KB bytes as blocks of 16 rows x 64 bytes,
-//     chunk-major, so a fragment read is a linear ds_read_b128.
+//   * A stage is 128 bytes of the contracted index.  Of A: BM rows of 128
+//     bytes, their 16-byte chunks XOR-swizzled by the row, so that an
+//     instruction fetches 8 whole lines and the rows one pass of a fragment
+//     read touches hit distinct banks.  (16 rows of 64 bytes per instruction, whose
+//     fragment reads are linear, took f16 1280^3 15.5 instead of 11.8 us, and
+//     128 x 128 tiles with five such stages of 64 bytes took f16 2560^3 62
+//     instead of 47: lines fetched in halves.)
 //   * A stage of B: the stage's rows of BN columns, row-major, 16-byte chunks
 //     XOR-swizzled by the row (ring_b_swz) so that the lanes of one pass of a
 //     transposing read hit distinct banks.
@@ -508,21 +513,21 @@ __device__ __forceinline__ int ring_b_swz(int k) {
   }
 }
 
-// Wait until at most 4 * min(later, kMax) of this wave's DMA loads are in
+// Wait until at most kPer * min(later, kMax) of this wave's DMA loads are in
 // flight (and its LDS reads returned), then barrier.
-template <int kMax>
+template <int kMax, int kPer>
 __device__ __forceinline__ void ring_wait(int later) {
   if constexpr (kMax == 0) {
     vm_wait_barrier<0>();
   } else {
     if (later >= kMax)
-      vm_wait_barrier<4 * kMax>();
+      vm_wait_barrier<kPer * kMax>();
     else
-      ring_wait<kMax - 1>(later);
+      ring_wait<kMax - 1, kPer>(later);
   }
 }
 
-template <int DT, int BM, int BN, int KB, int kStages, bool kDma>
+template <int DT, int BM, int BN, int kStages, bool kDma>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, BM == 64 ? (kDma ? 3 : 4) : 2))) void
 gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
                  unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
@@ -530,14 +535,14 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   constexpr bool kI8 = in_bytes(DT) == 1;
   constexpr int ES = in_bytes(DT), OB = out_bytes(DT);
   constexpr int EPC = 16 / ES;
+  constexpr int KB = 128;                        // bytes of the contracted index per stage
   constexpr int KE = KB / ES;                    // contracted elements per stage
   constexpr int KK = KB / 64;                    // matrix-core K steps per stage
   constexpr int BROW = BN * ES;                  // bytes per B row of a stage
   constexpr int kAStage = BM * KB, kBStage = BN * KB;
   constexpr int JA = kAStage / 4096, JB = kBStage / 4096;   // 1 KiB pieces per wave
   constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16;
-  static_assert(!kDma || JA + JB == 4, "the stage waits count 4 DMA loads per wave");
-  static_assert(!kDma || 4 * (kStages - 2) <= 63, "vmcnt range");
+  static_assert(!kDma || (JA + JB) * (kStages - 2) <= 63, "vmcnt range");
   static_assert(kDma || kStages == 2, "register-staged: two slots");
   typedef typename std::conditional<kI8, i32x4, f32x4>::type Acc;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kStages * (kAStage + kBStage)];
@@ -568,11 +573,10 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   const int nk = (int)((int64_t)nk_all * (slice + 1) / nsplit) - s_begin;
   const int k_first = s_begin * KE;
 
-  // Piece j of a stage of A: rows 16 (j / KK) + lane % 16, chunk 4 (j % KK) +
-  // lane / 16, at LDS bytes 1024 j + 16 lane.  Piece j of B: LDS bytes
-  // [1024 j, 1024 (j + 1)) of the row-major swizzled stage.
-  auto a_row = [&](int j) { return 16 * (j / KK) + (lane & 15); };
-  auto a_chunk = [&](int j) { return 4 * (j % KK) + (lane >> 4); };
+  // Piece j of a stage: LDS bytes [1024 j, 1024 (j + 1)), lane by lane -- of A
+  // rows 8 j + lane / 8, of B the rows that lie there.
+  auto a_row = [&](int j) { return 8 * j + (lane >> 3); };
+  const int a_chunk = (lane & 7) ^ (lane >> 3);
   auto b_row = [&](int j) { return (1024 * j + 16 * lane) / BROW; };
   auto b_chunk = [&](int j) {
     return (((1024 * j + 16 * lane) % BROW) / 16) ^ ring_b_swz<ES, BROW>(b_row(j));
@@ -585,7 +589,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   if constexpr (kDma) {
 #pragma unroll
     for (int i = 0; i < JA; ++i)
-      aoff[i] = (unsigned)(min(a_row(w * JA + i), M - 1 - m0) * lda_b) + 16u * a_chunk(w * JA + i);
+      aoff[i] = (unsigned)(min(a_row(w * JA + i), M - 1 - m0) * lda_b) + 16u * a_chunk;
 #pragma unroll
     for (int i = 0; i < JB; ++i)
       boff[i] = (unsigned)(b_row(w * JB + i) * ldb_b) + 16u * min(b_chunk(w * JB + i), c_last);
@@ -601,7 +605,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
 #pragma unroll
   for (int i = 0; i < JA; ++i)
     pa[i] = A + (int64_t)min(m0 + a_row(w * JA + i), M - 1) * lda_b + (int64_t)k_first * ES +
-            16 * a_chunk(w * JA + i);
+            16 * a_chunk;
 #pragma unroll
   for (int i = 0; i < JB; ++i) {
     const int c = n0 + b_chunk(w * JB + i) * EPC, cc = short_rows ? c : min(c, N - EPC);
@@ -632,7 +636,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
 #pragma unroll
       for (int i = 0; i < JA; ++i) {
         // the last chunk inside the row may start before this stage
-        const int c = a_chunk(w * JA + i) * EPC, back = c - min(c, kleft - EPC);
+        const int c = a_chunk * EPC, back = c - min(c, kleft - EPC);
         const u32x4 v = shift_down(load16_any(pa[i] + at - back * ES), (back * ES) & 15);
         ra[i] = c < kleft ? v : u32x4{0u, 0u, 0u, 0u};
       }
@@ -647,7 +651,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
 #pragma unroll
     for (int i = 0; i < JA; ++i)
       ra[i] = load_chunk<ES, false>(pa[i] + at,
-                                    max(min(kleft - a_chunk(w * JA + i) * EPC, EPC), 0));
+                                    max(min(kleft - a_chunk * EPC, EPC), 0));
 #pragma unroll
     for (int i = 0; i < JB; ++i) {
       const int nleft = N - n0 - b_chunk(w * JB + i) * EPC;
@@ -672,7 +676,10 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   };
 
   // Fragment offsets within a stage: A rows WTM wm .., B^T columns WTN wn ..
-  const int x_off = wm * FM * KK * 1024 + 16 * lane;
+  int x_off[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk)
+    x_off[kk] = (wm * WTM + r) * KB + 16 * ((4 * kk + g) ^ (r & 7));
   int w_off[FN];
 #pragma unroll
   for (int fn = 0; fn < FN; ++fn) {
@@ -702,7 +709,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
     for (int kk = 0; kk < KK; ++kk) {
       u32x4 xf[FM], wf[FN];
 #pragma unroll
-      for (int fm = 0; fm < FM; ++fm) xf[fm] = *(const u32x4 *)(sa + x_off + (fm * KK + kk) * 1024);
+      for (int fm = 0; fm < FM; ++fm) xf[fm] = *(const u32x4 *)(sa + x_off[kk] + fm * 16 * KB);
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn) {
         u32x2 w0, w1;
@@ -736,7 +743,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
       // stay in flight); the barrier makes every wave's share visible and
       // ensures all waves finished reading stage t-1, whose slot is refilled.
       const int later = nk - 1 - t < kStages - 2 ? nk - 1 - t : kStages - 2;
-      ring_wait<kStages - 2>(later);
+      ring_wait<kStages - 2, JA + JB>(later);
       const int refill = t + kStages - 1;
       if (refill < nk) issue(slot == 0 ? kStages - 1 : slot - 1, refill);
       compute(slot);
@@ -908,10 +915,10 @@ hipError_t zero_tail(unsigned char *C, int64_t ldc_b, int tm, int tn, int full, 
 }
 
 // The ring kernel with kTile x kTile tiles and nsplit K ranges.  A CU holds
-// two workgroups of 128 x 128 tiles (DMA: five 64-byte stages each) or three
-// of 64 x 64 (DMA: three 128-byte stages; with eight stages and one
-// workgroup per CU, order 1024 took 9.7 instead of 8.6 us and order 1120,
-// whose 324 tiles then run in two rounds, 18.6 instead of 12.2 us).
+// two workgroups of 128 x 128 tiles (two stages each) or three of 64 x 64 (DMA:
+// three stages; with eight and one workgroup per CU, order 1024 took 9.7
+// instead of 8.6 us and order 1120, whose 324 tiles then run in two rounds,
+// 18.6 instead of 12.2).
 template <int DT, int kTile, bool kDma>
 hipError_t launch_ring(const RectArgs &a, int nsplit, hipStream_t stream, int num_cus) {
   const int tiles_m = (int)((a.M + kTile - 1) / kTile), tiles_n = (int)((a.N + kTile - 1) / kTile);
@@ -919,9 +926,8 @@ hipError_t launch_ring(const RectArgs &a, int nsplit, hipStream_t stream, int nu
     const hipError_t e = zero_view(a, stream, num_cus);
     if (e != hipSuccess) return e;
   }
-  constexpr int KB = kDma && kTile == 128 ? 64 : 128;
-  constexpr int kStages = !kDma ? 2 : kTile == 128 ? 5 : 3;
-  hipLaunchKernelGGL((gemm_ring_kernel<DT, kTile, kTile, KB, kStages, kDma>),
+  constexpr int kStages = kDma && kTile == 64 ? 3 : 2;
+  hipLaunchKernelGGL((gemm_ring_kernel<DT, kTile, kTile, kStages, kDma>),
                      dim3(tiles_m * tiles_n * nsplit), dim3(256), 0, stream,
                      (const unsigned char *)a.A, (const unsigned char *)a.B,
                      (unsigned char *)a.C, (int)a.M, (int)a.N, (int)a.K, a.lda, a.ldb, a.ldc,
@@ -947,11 +953,12 @@ GemmPath gemm_path() {
 // (microseconds) of t tiles whose contracted index is n64 pieces of 64 bytes
 // on `cus` compute units.  The constants are measured per 64-byte piece; both
 // sides at the sizes where the choice turns (us; full tile / 128 / 64):
-//   bf16 N = 1024: 30 / 15.6 / 8.6     N = 1536: - / 21.4 / 25.0
-//        N = 2048: 50 / 27.7 / 40.3    N = 2560: 64 / 57 / -
-//        N = 3072: 74 / 95 / 151       N = 4096: 108 / 167 / 332
-//   int8 N = 1536: - / 14.4 / 15.1     N = 2560: 39 / 34 / -
-//        N = 3072: 48 / 56 / 127
+//   bf16 N = 1024: 31 / 14.4 / 9.0     N = 1536: 43 / 20.3 / 18.1
+//        N = 2048: 50 / 27.4 / 33.0    N = 2560: 64 / 42 / 62
+//        N = 3072: 73 / 79 / 95        N = 4096: 110 / 132 / 220
+//   int8 N = 1536: 28 / 13.7 / 13.6    N = 2560: 39 / 26 / 41
+//        N = 3072: 44 / 47 / 74        N = 4096: 64 / 73 / 190
+// Filled through registers the ring kernel takes 1.1 to 1.25 times as long.
 // Split ranges are added atomically, after zeroing C when overwriting:
 // f16 192 x 8192 x 320 (15 tiles of 64) 37 us whole, 10.4 with 16 ranges,
 // 12.9 with 32; bf16 N = 3072 full-tile 74 whole, 135 with 2 ranges.
@@ -974,16 +981,16 @@ double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool sp
     }
     case Tile::k128: {
       // two workgroups per CU, which share its LDS bandwidth
-      const double pair = 0.65 * n64 + 5, single = 0.36 * n64 + 4;
+      const double pair = 0.44 * n64 + 5, single = 0.33 * n64 + 4;
       const int64_t rem = t % (2 * cus);
       const double us =
           (double)(t / (2 * cus)) * pair + (rem > cus ? pair : rem > 0 ? single : 0.0);
-      return dma ? us : 1.1 * us;
+      return dma ? us : 1.22 * us;
     }
     default: {
       // several workgroups per CU; below one per CU the latency of a stage
       const double per_cu = t > cus ? (double)t / (double)cus : 1.0;
-      const double stage = 0.04 + 0.16 * per_cu;
+      const double stage = 0.04 + 0.105 * per_cu;
       return n64 * (dma || stage > 0.24 ? stage : 0.24) + 1.5 * per_cu;
     }
   }
