@@ -82,29 +82,17 @@ __device__ __forceinline__ i32x4 mfma_i8_k32(u32x2 w, u32x2 x, i32x4 d) {
 // ---------------------------------------------------------------- LDS
 #define TCU_LDS(T, p) ((__attribute__((address_space(3))) T *)(p))
 
-// Direct global -> LDS copy of 16 bytes per lane: lane l's bytes land at
-// lds_base + 16*l (lds_base must be wave-uniform).
-__device__ __forceinline__ void load_lds16(const void *gptr, void *lds_base) {
-  __builtin_amdgcn_global_load_lds(gptr, TCU_LDS(void, lds_base), 16, 0, 0);
-}
-
 // LDS byte address of a __shared__ object.
 __device__ __forceinline__ unsigned lds_addr(const void *p) {
   return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
 }
 
-// The same direct copy issued as an instruction the compiler cannot see
-// into: it then inserts no waits of its own for it, so a multi-stage ring in
+// Direct global -> LDS copy of 16 bytes per lane from a wave-uniform 64-bit
+// base plus a per-lane 32-bit offset: lane l's bytes land at lds_base + 16 l
+// (a wave-uniform LDS address).  Issued as an instruction the compiler cannot
+// see into: it then inserts no waits of its own for it, so a multi-stage ring in
 // one LDS array keeps its later stages in flight.  The caller orders it with
-// explicit vmcnt waits and barriers.  lds_base: wave-uniform LDS address.
-__device__ __forceinline__ void dma_lds16(const void *gptr, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(gptr), "s"(lds_base)
-               : "memory", "m0");
-}
-
-// The same with a wave-uniform 64-bit base and a per-lane 32-bit offset.
+// explicit vmcnt waits and barriers.
 __device__ __forceinline__ void dma_lds16_saddr(const void *gbase, unsigned voff,
                                                 unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
@@ -278,23 +266,6 @@ __device__ __forceinline__ void store_sum4(unsigned char *p, Acc v, Old4<DT> o) 
     *(u32x4 *)p = bitcast<u32x4>(v) + o;
   } else {
     *(u32x4 *)p = bitcast<u32x4>(bitcast<f32x4>(v) + bitcast<f32x4>(o));
-  }
-}
-
-// Add 4 consecutive partial sums into C at p with device-scope atomic adds
-// (binary32 or int32; split-K partial tiles).  Not for bfloat16 outputs,
-// which must be rounded once from the whole sum.
-template <int DT, typename Acc>
-__device__ __forceinline__ void atomic_add_out4(unsigned char *p, Acc v) {
-  static_assert(DT == TCU_F16_F32 || DT == TCU_BF16_F32 || DT == TCU_I8_I32,
-                "only binary32 and int32 outputs are split");
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    if constexpr (DT == TCU_I8_I32)
-      __hip_atomic_fetch_add((int *)p + e, (int)v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-      __hip_atomic_fetch_add((float *)p + e, (float)v[e], __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 

@@ -19,6 +19,8 @@
 // operand, so each lane holds 4 consecutive columns of one row of C, stored
 // as one 16-byte write.
 // Workgroup order is XCD-aware (see map_tile).
+#include <climits>
+
 #include "tcu_device.h"
 #include "tcu_launch.h"
 
@@ -527,11 +529,16 @@ __device__ __forceinline__ void ring_wait(int later) {
   }
 }
 
+constexpr int ring_lds(int tile, int stages) { return stages * 2 * tile * 128; }
+
+// One work item: the BM x BN tile of C at (m0, n0), K range `slice` of nsplit,
+// on ring_lds bytes of LDS.
 template <int DT, int BM, int BN, int kStages, bool kDma>
-__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, BM == 64 ? (kDma ? 3 : 4) : 2))) void
-gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
-                 unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
-                 int64_t ldc, int accum, int tiles_m, int tiles_n, int nsplit) {
+__device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned char *__restrict__ A,
+                                          const unsigned char *__restrict__ B,
+                                          unsigned char *__restrict__ C, int M, int N, int K,
+                                          int64_t lda, int64_t ldb, int64_t ldc, int accum,
+                                          int m0, int n0, int slice, int nsplit) {
   constexpr bool kI8 = in_bytes(DT) == 1;
   constexpr int ES = in_bytes(DT), OB = out_bytes(DT);
   constexpr int EPC = 16 / ES;
@@ -545,7 +552,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   static_assert(!kDma || (JA + JB) * (kStages - 2) <= 63, "vmcnt range");
   static_assert(kDma || kStages == 2, "register-staged: two slots");
   typedef typename std::conditional<kI8, i32x4, f32x4>::type Acc;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kStages * (kAStage + kBStage)];
+  static_assert(kStages * (kAStage + kBStage) == ring_lds(BM, kStages), "square tiles");
   unsigned char *const sA = smem;
   unsigned char *const sB = smem + kStages * kAStage;
 
@@ -553,20 +560,6 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int r = lane & 15, g = lane >> 4;
-  const int tiles = tiles_m * tiles_n;
-  // Split items go K range by K range, permuted so that each XCD holds a
-  // contiguous run of them (its L2 then serves one range's panels); the
-  // items past the last multiple of 8 keep their ids.
-  int pid = blockIdx.x, slice = 0;
-  if (nsplit > 1) {
-    const int body = tiles * nsplit / 8 * 8;
-    if (pid < body) pid = (pid % 8) * (body / 8) + pid / 8;
-    slice = pid / tiles;
-    pid -= slice * tiles;
-  }
-  int tm, tn;
-  map_tile(pid, tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
   const int64_t lda_b = lda * ES, ldb_b = ldb * ES, ldc_b = ldc * OB;
   const int nk_all = (K + KE - 1) / KE;
   const int s_begin = (int)((int64_t)nk_all * slice / nsplit);
@@ -769,14 +762,14 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
 
   // Epilogue: lane holds C[row][col .. col+3] of every accumulator block.
   constexpr bool kSplittable = DT == TCU_F16_F32 || DT == TCU_BF16_F32 || DT == TCU_I8_I32;
+  constexpr int kStride = WTN * 4 + 16;
+  unsigned char *stage = smem + w * 32 * kStride;
+  static_assert(4 * 32 * kStride <= kStages * (kAStage + kBStage), "staging fits the ring");
   if constexpr (kSplittable) {
     if (nsplit > 1) {
       // Partial tiles are added into C atomically, through this wave's part
       // of LDS so that one atomic instruction covers whole runs of a row.
-      constexpr int kStride = WTN * 4 + 16;
       constexpr int kRowsPer = 64 / WTN;         // rows per atomic instruction
-      unsigned char *stage = smem + w * 32 * kStride;
-      static_assert(4 * 32 * kStride <= kStages * (kAStage + kBStage), "staging fits the ring");
       __syncthreads();   // every wave finished reading the ring
       const int col = n0 + wn * WTN + lane % WTN;
 #pragma unroll
@@ -806,6 +799,42 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
       return;
     }
   }
+  if constexpr (!kDma && OB == 2 && BM == 128) {
+    if ((((uintptr_t)C | (uintptr_t)ldc_b) & (4 * OB - 1)) != 0) {
+      // 16-bit rows that start anywhere go through LDS too: in the accumulator
+      // layout a store is 16 runs of 32 bytes, most of them across sectors;
+      // here its runs are the sub-tile's whole rows.  us, direct -> staged:
+      // 4101 x 1000 x 4173 71.6 -> 68.5, 3072 x 200 x 3071 20.7 -> 16.8.
+      // 4-byte outputs do not gain (3072 x 1000 x 3071 39.6 -> 40.2), and 64 x
+      // 64 tiles lose to the barriers (1001 x 1003 x 1005 10.4 -> 11.0).
+      constexpr int kRowLanes = WTN / 4, kRowsPer = 64 / kRowLanes;
+      const int col = n0 + wn * WTN + 4 * (lane % kRowLanes);
+      const int valid = min(max(N - col, 0), 4);
+      __syncthreads();   // every wave finished reading the ring
+#pragma unroll
+      for (int h = 0; h < FM / 2; ++h) {
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+          for (int fm = 0; fm < 2; ++fm)
+            *(Acc *)(stage + (fm * 16 + r) * kStride + (fn * 16 + 4 * g) * 4) =
+                acc[fn][2 * h + fm];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 32; i += kRowsPer) {
+          const int in = i + lane / kRowLanes, row = m0 + wm * WTM + 32 * h + in;
+          const Acc v = *(const Acc *)(stage + in * kStride + (lane % kRowLanes) * 16);
+          unsigned char *p = C + (int64_t)row * ldc_b + (int64_t)col * OB;
+          if (row < M && valid == 4)
+            store_out4<DT, true>(p, v, 4, accum != 0);
+          else if (row < M && valid > 0)
+            store_out4<DT, false>(p, v, valid, accum != 0);
+        }
+        __syncthreads();   // reads done before the next rows overwrite
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int fm = 0; fm < FM; ++fm) {
 #pragma unroll
@@ -820,6 +849,51 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
         store_out4<DT, false>(p, acc[fn][fm], valid, accum != 0);
     }
   }
+}
+
+// Work items are (K range, tile) pairs.  kCut (128 x 128, unsplit): the tiles from
+// `whole` on are cut into four quarters of 64 x 64, items of their own (empty past
+// the edge of C), so that a last round of few tiles is spread over the chip.  An
+// instance apart: with both bodies in one, whole tiles took f16 3328 x 1024 x
+// 3328 35.0 instead of 33.8 us.
+template <int DT, int kTile, int kStages, bool kDma, bool kCut>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256),
+                          amdgpu_waves_per_eu(1, kTile == 64 ? (kDma ? 3 : 4) : 2))) void
+gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
+                 unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
+                 int64_t ldc, int accum, int tiles_m, int tiles_n, int nsplit, int whole) {
+  constexpr int kQuarterStages = kDma ? 4 : 2;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[ring_lds(kTile, kStages)];
+  const int tiles = tiles_m * tiles_n;
+  // Split items go K range by K range, permuted so that each XCD holds a
+  // contiguous run of them (its L2 then serves one range's panels); the
+  // items past the last multiple of 8 keep their ids.
+  int pid = blockIdx.x, slice = 0, quarter = 0;
+  const bool cut = kCut && pid >= whole;
+  if (!kCut && nsplit > 1) {
+    const int body = tiles * nsplit / 8 * 8;
+    if (pid < body) pid = (pid % 8) * (body / 8) + pid / 8;
+    slice = pid / tiles;
+    pid -= slice * tiles;
+  } else if (cut) {
+    quarter = (pid - whole) & 3;
+    pid = whole + ((pid - whole) >> 2);
+  }
+  int tm, tn;
+  map_tile(pid, tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * kTile, n0 = tn * kTile;
+  if constexpr (kCut) {
+    static_assert(ring_lds(64, kQuarterStages) <= ring_lds(kTile, kStages), "a quarter's ring");
+    if (cut) {
+      const int mq = m0 + 64 * (quarter >> 1), nq = n0 + 64 * (quarter & 1);
+      if (mq < M && nq < N)
+        ring_tile<DT, 64, 64, kQuarterStages, kDma>(smem, A, B, C, M, N, K, lda, ldb, ldc, accum,
+                                                    mq, nq, 0, 1);
+      return;
+    }
+  }
+  ring_tile<DT, kTile, kTile, kStages, kDma>(smem, A, B, C, M, N, K, lda, ldb, ldc, accum, m0, n0,
+                                             slice, kCut ? 1 : nsplit);
 }
 
 // Zero the rows x row_words view of 4-byte words at C (row pitch ldc_w
@@ -914,24 +988,34 @@ hipError_t zero_tail(unsigned char *C, int64_t ldc_b, int tm, int tn, int full, 
   return hipGetLastError();
 }
 
-// The ring kernel with kTile x kTile tiles and nsplit K ranges.  A CU holds
+// The ring kernel with kTile x kTile tiles and nsplit K ranges, tiles from
+// `whole` on in quarters (128 x 128, unsplit).  A CU holds
 // two workgroups of 128 x 128 tiles (two stages each) or three of 64 x 64 (DMA:
 // three stages; with eight and one workgroup per CU, order 1024 took 9.7
 // instead of 8.6 us and order 1120, whose 324 tiles then run in two rounds,
 // 18.6 instead of 12.2).
 template <int DT, int kTile, bool kDma>
-hipError_t launch_ring(const RectArgs &a, int nsplit, hipStream_t stream, int num_cus) {
+hipError_t launch_ring(const RectArgs &a, int nsplit, int whole, hipStream_t stream,
+                       int num_cus) {
   const int tiles_m = (int)((a.M + kTile - 1) / kTile), tiles_n = (int)((a.N + kTile - 1) / kTile);
   if (nsplit > 1 && !a.accum) {
     const hipError_t e = zero_view(a, stream, num_cus);
     if (e != hipSuccess) return e;
   }
   constexpr int kStages = kDma && kTile == 64 ? 3 : 2;
-  hipLaunchKernelGGL((gemm_ring_kernel<DT, kTile, kTile, kStages, kDma>),
-                     dim3(tiles_m * tiles_n * nsplit), dim3(256), 0, stream,
-                     (const unsigned char *)a.A, (const unsigned char *)a.B,
-                     (unsigned char *)a.C, (int)a.M, (int)a.N, (int)a.K, a.lda, a.ldb, a.ldc,
-                     a.accum ? 1 : 0, tiles_m, tiles_n, nsplit);
+  const int tiles = tiles_m * tiles_n;
+  if (whole > tiles || nsplit > 1) whole = tiles;
+  auto go = [&](auto cut, int items) {
+    hipLaunchKernelGGL((gemm_ring_kernel<DT, kTile, kStages, kDma, decltype(cut)::value>),
+                       dim3(items), dim3(256), 0, stream, (const unsigned char *)a.A,
+                       (const unsigned char *)a.B, (unsigned char *)a.C, (int)a.M, (int)a.N,
+                       (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0, tiles_m, tiles_n, nsplit,
+                       whole);
+  };
+  if (kTile == 128 && whole < tiles)
+    go(std::integral_constant<bool, kTile == 128>{}, whole + 4 * (tiles - whole));
+  else
+    go(std::false_type{}, tiles * nsplit);
   return hipGetLastError();
 }
 
@@ -970,7 +1054,9 @@ struct Choice {
   double us = 1e30;
 };
 
-double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool splittable) {
+// *cut: whether the tiles of a last, partial round are cut into quarters (128).
+double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool splittable,
+                bool *cut = nullptr) {
   switch (tile) {
     case Tile::kFull: {
       // one workgroup per CU, whole rounds; the last may be split
@@ -983,9 +1069,19 @@ double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool sp
       // two workgroups per CU, which share its LDS bandwidth
       const double pair = 0.44 * n64 + 5, single = 0.33 * n64 + 4;
       const int64_t rem = t % (2 * cus);
-      const double us =
-          (double)(t / (2 * cus)) * pair + (rem > cus ? pair : rem > 0 ? single : 0.0);
-      return dma ? us : 1.22 * us;
+      const double rounds = (double)(t / (2 * cus)) * pair * (dma ? 1.0 : 1.22);
+      const double last = (rem > cus ? pair : rem > 0 ? single : 0.0) * (dma ? 1.0 : 1.22);
+      if (cut) *cut = false;
+      if (t < 2 * cus || rem == 0) return rounds + last;
+      // The tiles of a last round of at most cus / 2 are cut into quarters, two
+      // per CU at most, which take about 0.6 of a tile's time (us, whole / cut;
+      // odd pitches, bf16: 3072 x 1000 x 3071, 64 tiles, 45.9 / 40.2; 3200 x
+      // 1000 x 3199, 113 tiles, 45.7 / 42.9; 3328 x 1000 x 3327, 164 tiles,
+      // 46.1 / 50.7; by DMA 3072 x 2048 x 3072, 64 tiles, 56.7 / 46.7; 3200 x
+      // 512 x 3200, 113 tiles, 23.9 / 21.5; 3328 x 1024 x 3328 35.3 / 36.2).
+      if (2 * rem > cus) return rounds + last;
+      if (cut) *cut = true;
+      return rounds + 0.6 * last;
     }
     default: {
       // several workgroups per CU; below one per CU the latency of a stage
@@ -1036,7 +1132,7 @@ bool ring_dma_ok(const RectArgs &a) {
 
 template <int DT>
 hipError_t launch_ring_choice(const RectArgs &a, bool dma, const Choice &c, hipStream_t stream,
-                              int num_cus) {
+                              int num_cus, int64_t cus) {
   // Test override of the ranges (at most one per 128-byte stage).
   int ns = c.nsplit;
   const int forced = knob(TCU_KNOB_SPLIT_K);
@@ -1044,11 +1140,17 @@ hipError_t launch_ring_choice(const RectArgs &a, bool dma, const Choice &c, hipS
     const int64_t stages = (a.K * in_bytes(DT) + 127) / 128;
     ns = (int)(forced < stages ? forced : stages > 1 ? stages : 1);
   }
-  if (c.tile == Tile::k128)
-    return dma ? launch_ring<DT, 128, true>(a, ns, stream, num_cus)
-               : launch_ring<DT, 128, false>(a, ns, stream, num_cus);
-  return dma ? launch_ring<DT, 64, true>(a, ns, stream, num_cus)
-             : launch_ring<DT, 64, false>(a, ns, stream, num_cus);
+  if (c.tile == Tile::k128) {
+    const int64_t t = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+    const int64_t n64 = (a.K * in_bytes(DT) + 63) / 64;
+    bool cut = false;
+    model_us(Tile::k128, dma, t, (double)n64, cus, false, &cut);
+    const int whole = (int)(cut ? t - t % (2 * cus) : t);
+    return dma ? launch_ring<DT, 128, true>(a, ns, whole, stream, num_cus)
+               : launch_ring<DT, 128, false>(a, ns, whole, stream, num_cus);
+  }
+  return dma ? launch_ring<DT, 64, true>(a, ns, INT_MAX, stream, num_cus)
+             : launch_ring<DT, 64, false>(a, ns, INT_MAX, stream, num_cus);
 }
 
 template <int DT>
@@ -1056,7 +1158,7 @@ hipError_t launch_general(const RectArgs &a, GemmPath path, hipStream_t stream, 
                           int64_t cus) {
   const bool dma = path != GemmPath::kGeneral && ring_dma_ok<DT>(a);
   return launch_ring_choice<DT>(a, dma, choose_ring<DT>(a, dma, path == GemmPath::kRing, cus),
-                                stream, num_cus);
+                                stream, num_cus, cus);
 }
 
 // The full-tile kernel on tm x tn tiles of C (all of it, or its 256-aligned
@@ -1155,7 +1257,7 @@ hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
     }
     if (full.us < best.us) best = full;
   }
-  if (best.tile != Tile::kFull) return launch_ring_choice<DT>(a, dma, best, stream, num_cus);
+  if (best.tile != Tile::kFull) return launch_ring_choice<DT>(a, dma, best, stream, num_cus, cus);
   if (whole)
     return launch_full<DT, false>(a, (int)tm, (int)tn, best.nsplit, stream, num_cus);
   hipError_t e = launch_full<DT, true>(a, (int)tm, (int)tn, 1, stream, num_cus);

@@ -51,3 +51,17 @@ def test_ring_split_k_chosen_by_size(din, out, cus, knobs):
     """A few tiles with a long K are split without forcing."""
     knobs(tcu.TCU_KNOB_PP_GRID, cus)
     run_and_check(131, 8200, 140, din, out, 16, "contiguous", True, seed=9)
+
+
+# On 2 compute units a round is 4 tiles of 128 x 128 and a last round of one is cut
+# into quarters of 64 x 64: 5 and 9 tiles whose last has four, two or one quarter
+# inside C, one of them a row or a column wide; DMA and register-staged.
+@pytest.mark.parametrize("pitch", ["contiguous", "padded"])
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("din,out", PAIRS)
+@pytest.mark.parametrize("M,K,N", [(640, 128, 128), (600, 130, 101), (577, 2055, 112),
+                                   (321, 333, 384), (384, 64, 321), (300, 70, 304), (1030, 99, 60)])
+def test_ring_quarters(M, K, N, din, out, accumulate, pitch, knobs):
+    knobs(tcu.TCU_KNOB_GEMM_KERNEL, gu.PATHS["auto"])
+    knobs(tcu.TCU_KNOB_PP_GRID, 2)
+    run_and_check(M, K, N, din, out, 16, pitch, accumulate, seed=M + K * 3 + N)
