@@ -743,7 +743,14 @@ hipError_t launch_pair(const f32x2 *src, f32x2 *dst, int64_t n, int64_t P, int64
   // 118 us, n = 2^16, batch 256, s = 16 128 -> 114 us; n = 2^20, batch 2 (16
   // MiB) loses, 23.2 -> 24.9 us, batch 4 gains, 34.1 -> 31.1.
   const bool stream_in = batch * n * 8 >= (int64_t)32 << 20;
-  if (P >= 16)
+  // Later pairs read the other buffer for the last time, past the caches from
+  // 64 MiB on: its lines then make room for the output's.  n = 2^20, batch 16
+  // 113.1 -> 110.2 us, batch 8 58.7 -> 57.2; batch 4 (32 MiB) 30.8 both.
+  const bool stream_work = batch * n * 8 >= (int64_t)64 << 20;
+  if (P >= 16 && stream_work)
+    hipLaunchKernelGGL((dft_pair_kernel<S, true, true>), dim3(blocks), dim3(kPairThreads), 0,
+                       stream, src, dst, ilog2(n), ilog2(P), ntiles, last2 ? 1 : 0);
+  else if (P >= 16)
     hipLaunchKernelGGL((dft_pair_kernel<S, true, false>), dim3(blocks), dim3(kPairThreads), 0,
                        stream, src, dst, ilog2(n), ilog2(P), ntiles, last2 ? 1 : 0);
   else if (stream_in)
