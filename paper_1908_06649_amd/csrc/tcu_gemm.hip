@@ -854,7 +854,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
 // Work items are (K range, tile) pairs.  kCut (128 x 128, unsplit): the tiles from
 // `whole` on are cut into four quarters of 64 x 64, items of their own (empty past
 // the edge of C), so that a last round of few tiles is spread over the chip.  An
-// instance apart: with both bodies in one, whole tiles took f16 3328 x 1024 x
+// instance apart: with both bodies in one, whole tiles took bf16 3328 x 1024 x
 // 3328 35.0 instead of 33.8 us.
 template <int DT, int kTile, int kStages, bool kDma, bool kCut>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256),
@@ -1042,6 +1042,7 @@ GemmPath gemm_path() {
 //        N = 3072: 73 / 79 / 95        N = 4096: 110 / 132 / 220
 //   int8 N = 1536: 28 / 13.7 / 13.6    N = 2560: 39 / 26 / 41
 //        N = 3072: 44 / 47 / 74        N = 4096: 64 / 73 / 190
+// (N = 3072's last round of 64 tiles whole; in quarters int8 takes 41.)
 // Filled through registers the ring kernel takes 1.1 to 1.25 times as long.
 // Split ranges are added atomically, after zeroing C when overwriting:
 // f16 192 x 8192 x 320 (15 tiles of 64) 37 us whole, 10.4 with 16 ranges,
