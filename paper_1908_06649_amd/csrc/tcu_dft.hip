@@ -33,7 +33,12 @@
 // each; the weights operand is W_S (rows = output frequency k, contracted index
 // j), formed once per wave.  A last level of radix R < S takes S/R transforms
 // per column, its weights S/R diagonal blocks W_R (a column of one transform
-// would leave S - R of its elements empty).  Complex products are real products
+// would leave S - R of its elements empty).  The zeros between the blocks keep
+// the transforms of a column apart only while every word is finite (0 x Inf is
+// NaN), so an element that is not is replaced by zero and every output of its
+// transform by NaN, what the products with its words would give
+// (dft_set_apart): an infinite or NaN value, or one past bfloat16's range,
+// reaches its own transform alone.  Complex products are real products
 // on the bf16 matrix cores: Re = Wr Xr - Wi Xi, Im = Wi Xr + Wr Xi.  The data
 // and W each enter as the sum of two bf16 words (hi + lo), and every real
 // product is formed as hi*hi + hi*lo + lo*hi into binary32 accumulators, about
@@ -185,6 +190,48 @@ __device__ __forceinline__ void dft_data(DftData<S> &X, const float *xr, const f
     split_bf16x2(xi[2 * q], xi[2 * q + 1], hi, lo, sc);
     X.xi_h[q] = hi;
     X.xi_l[q] = lo;
+  }
+}
+// Elements of a narrow level's column that are not finite as bfloat16 words
+// (Inf, NaN, or a magnitude that rounds to Inf): whether a lane holds one, the
+// largest magnitude of its elements (NaN if one is) given ...
+constexpr unsigned kDftLimit = 0x7f7f8000u;   // halfway from the largest bfloat16 to Inf
+template <int S>
+__device__ __forceinline__ float dft_largest(float m, const f32x2 (&v)[DftShape<S>::kRun]) {
+#pragma unroll
+  for (int e = 0; e < DftShape<S>::kRun; ++e)
+    m = __builtin_elementwise_maximum(
+        __builtin_elementwise_maximum(m, __builtin_fabsf(v[e][0])), __builtin_fabsf(v[e][1]));
+  return m;
+}
+__device__ __forceinline__ bool dft_not_finite(float largest) {
+  return !(largest < bitcast<float>(kDftLimit));
+}
+// ... and their replacement by zero; returns the column's set of transforms that
+// hold one, bit u for slots u R .. u R + R - 1.
+template <int S>
+__device__ __forceinline__ unsigned dft_set_apart(f32x2 (&v)[DftShape<S>::kRun], int g, int lg_r) {
+  unsigned set = 0;
+#pragma unroll
+  for (int e = 0; e < DftShape<S>::kRun; ++e) {
+    if (dft_not_finite(__builtin_elementwise_maximum(__builtin_fabsf(v[e][0]),
+                                                     __builtin_fabsf(v[e][1])))) {
+      v[e] = f32x2{0.f, 0.f};
+      set |= 1u << ((DftShape<S>::kRun * g + e) >> lg_r);
+    }
+  }
+  set |= (unsigned)__shfl_xor((int)set, 16);
+  return set | (unsigned)__shfl_xor((int)set, 32);
+}
+// NaN to this lane's outputs of the transforms in the set, after the others:
+// `put(k, nan)` stores output k (a rolled loop: this is the rare case).
+template <int S, typename Put>
+__device__ __forceinline__ void dft_put_spoilt(unsigned set, int g, int lg_r, Put put) {
+  const float nan = __builtin_nanf("");
+#pragma unroll 1
+  for (int j = 0; j < 4 * DftShape<S>::kH; ++j) {
+    const int k = 16 * (j >> 2) + 4 * g + (j & 3);
+    if (set >> (k >> lg_r) & 1u) put(k, f32x2{nan, nan});
   }
 }
 template <int S>
@@ -356,13 +403,20 @@ __global__ __launch_bounds__(kDftThreads) void dft_level_kernel(
   const int64_t nchunks = (ntrans + (16 << lg_sub) - 1) >> (4 + lg_sub);
   for (int64_t chunk = wave; chunk < nchunks; chunk += nwaves) {
     const LevelIndex<S, kNarrow, int64_t> at(lg_n, lg_r, lg_p, (chunk << (4 + lg_sub)) + r, g);
+    f32x2 v[kRun];
+#pragma unroll
+    for (int e = 0; e < kRun; ++e) {
+      v[e] = f32x2{0.f, 0.f};
+      if (at.trans(kRun * g + e) < ntrans) v[e] = src[at.in(e)];
+    }
+    const bool apart = kNarrow && __any(dft_not_finite(dft_largest<S>(0.f, v)));
+    unsigned spoilt = 0;
+    if (apart) spoilt = dft_set_apart<S>(v, g, lg_r);
     float xr[kRun], xi[kRun];
 #pragma unroll
     for (int e = 0; e < kRun; ++e) {
-      f32x2 v = {0.f, 0.f};
-      if (at.trans(kRun * g + e) < ntrans) v = src[at.in(e)];
-      xr[e] = v[0];
-      xi[e] = v[1];
+      xr[e] = v[e][0];
+      xi[e] = v[e][1];
     }
     DftData<S> X;
     dft_data<S>(X, xr, xi, sc);
@@ -388,6 +442,10 @@ __global__ __launch_bounds__(kDftThreads) void dft_level_kernel(
           if (at.trans(k0 + i) < ntrans) dst[at.out(k0 + i)] = y[i];
       }
     }
+    if (apart)
+      dft_put_spoilt<S>(spoilt, g, lg_r, [&](int k, f32x2 nan) {
+        if (at.trans(k) < ntrans) dst[at.out(k)] = nan;
+      });
   }
 }
 
@@ -636,6 +694,18 @@ dft_local_kernel(const f32x2 *__restrict__ src, f32x2 *__restrict__ dst, int lg_
 #pragma unroll
       for (int e = 0; e < kRun; ++e) v[i][e] = tile[local_at(at.in(e))];
     }
+    bool apart = false;
+    unsigned spoilt[kSteps];
+    if constexpr (kNarrow) {
+      float largest = 0.f;
+#pragma unroll
+      for (int i = 0; i < kSteps; ++i) largest = dft_largest<S>(largest, v[i]);
+      apart = __any(dft_not_finite(largest));
+      if (apart) {
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) spoilt[i] = dft_set_apart<S>(v[i], g, lg_r);
+      }
+    }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kSteps; ++i) {
@@ -667,6 +737,14 @@ dft_local_kernel(const f32x2 *__restrict__ src, f32x2 *__restrict__ dst, int lg_
         sf.apply(y, col, k0);
 #pragma unroll
         for (int e = 0; e < 4; ++e) tile[local_at(at.out(k0 + e))] = y[e];
+      }
+    }
+    if (apart) {
+#pragma unroll
+      for (int i = 0; i < kSteps; ++i) {
+        const Index at(lg_n, lg_r, lg_p, ((wv + kWaves * i) << (4 + lg_sub)) + r, g);
+        dft_put_spoilt<S>(spoilt[i], g, lg_r,
+                          [&](int k, f32x2 nan) { tile[local_at(at.out(k))] = nan; });
       }
     }
     __syncthreads();
