@@ -138,15 +138,15 @@ int tcu_mm_tall(const void *A, int64_t n, int s, const void *B, void *C);
  * Errors: as tcu_mm_tall, with TCU_ERR_SHAPE for N < s or N % s != 0.
  * On success the logical call counter advances by (N/s)^2 = n/m, the number
  * of calls of Theorem 2 (and its lower bound on right-matrix loads).
- * Reproducibility: int32 and bfloat16 results are the same on every call.
- * A binary32 result is too, unless the product splits the contracted index
- * across workgroups -- which it does where few output tiles with a long
- * contracted index would leave compute units idle, or where the 256 x 256
- * tiles do not fill a whole number of rounds of the persistent grid (the
- * tiles of the last round are then split) -- because the partial sums are
- * then added into C with atomic additions in no fixed order: the low bits
- * of such a binary32 result may differ from call to call (each result is
- * within the stated summation bound; the order-8192 products are not split). */
+ * Reproducibility: int32 and bfloat16 results are the same on every call, and
+ * so is every binary32 result with a contracted index (here N) below 2048.
+ * From 2048 on a binary32 product may be cut into ranges of the contracted
+ * index, taken by different workgroups -- where few output tiles would leave
+ * compute units idle, or where the 256 x 256 tiles do not fill a whole number
+ * of rounds of the persistent grid (the tiles of the last round are then cut)
+ * -- and their sums are added into C with atomic additions in no fixed order:
+ * the low bits of such a result may differ from call to call (each result is
+ * within the stated summation bound; the order-8192 products are not cut). */
 int tcu_gemm(const void *A, const void *B, void *C, int64_t N);
 
 /* Stateless forms of the two calls: unit size, dtype and stream are
@@ -191,10 +191,12 @@ int tcu_gemm_ex(const void *A, const void *B, void *C, int64_t N, int s,
  * same type and the result is stored once (rounded to nearest even for a
  * bfloat16 output).  For int8 inputs K < 2^17 is required, so A*B is exact
  * in int32; the accumulated C + A*B wraps modulo 2^32 if it leaves the
- * int32 range.  As for tcu_gemm, a binary32 result whose contracted index
- * is split across workgroups (few output tiles with a long K, or the tiles
- * of a partial last round) is summed in no fixed order, so its low bits may
- * differ from call to call; int32 and bfloat16 results are reproducible.
+ * int32 range.  As for tcu_gemm, a binary32 result with K >= 2048 may be
+ * summed in ranges in no fixed order (few output tiles, or the tiles of a
+ * partial last round; when accumulating, each range is added to C), so its low
+ * bits may differ from call to call.  With K < 2048, and for int32 and bfloat16
+ * outputs, every result is the same on every call: a caller who needs that of a
+ * longer product can accumulate pieces of it.
  * Layout rules: base pointers 16-byte aligned; every element each operand
  * addresses must lie below 2^40 bytes from its base.  Row pitches need no
  * alignment, but pitches whose byte size is a multiple of 16 (lda, ldb, ldc

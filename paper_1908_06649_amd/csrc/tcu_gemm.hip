@@ -39,11 +39,12 @@ constexpr int kRingStages = 5;
 // column-panels in its L2) while all XCDs together sweep a band of full rows
 // (B panels shared through the memory-side cache).  Measured best for N=8192
 // against larger groups and an explicit per-XCD remap of the ids.
+template <int kRows = kGroupM>
 __device__ __forceinline__ void map_tile(int pid, int tiles_m, int tiles_n, int &tm, int &tn) {
-  const int per_group = kGroupM * tiles_n;
+  const int per_group = kRows * tiles_n;
   const int group = pid / per_group;
-  const int first_m = group * kGroupM;
-  const int gsz = min(tiles_m - first_m, kGroupM);
+  const int first_m = group * kRows;
+  const int gsz = min(tiles_m - first_m, kRows);
   const int in_group = pid % per_group;
   tm = first_m + in_group % gsz;
   tn = in_group / gsz;
@@ -497,6 +498,16 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
 // (binary32 and int32 outputs).
 // ---------------------------------------------------------------------------
 
+// Wait until at most kPer * min(later, kMax) of this wave's DMA loads are in
+// flight.
+template <int kMax, int kPer>
+__device__ __forceinline__ void wave_wait(int later) {
+  if (kMax <= 0 || later >= kMax)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(kMax > 0 ? kPer * kMax : 0) : "memory");
+  else
+    wave_wait<(kMax > 0 ? kMax - 1 : 0), kPer>(later);
+}
+
 // XOR swizzle of the 16-byte chunks of row k of a B stage whose rows hold
 // `row_bytes` (64, 128 or 256) bytes.  A pass of 32 lanes of the transposing
 // read touches rows 0-3 and 8-11 (32 bytes each, 16-bit) or rows 0-7 and
@@ -505,9 +516,10 @@ gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restr
 template <int ES, int row_bytes>
 __device__ __forceinline__ int ring_b_swz(int k) {
   if constexpr (ES == 2) {
-    static_assert(row_bytes == 128 || row_bytes == 256, "B stage rows");
+    static_assert(row_bytes == 64 || row_bytes == 128 || row_bytes == 256, "B stage rows");
     if constexpr (row_bytes == 256) return ((k & 3) << 1) | (((k >> 3) & 1) << 3);
-    return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+    if constexpr (row_bytes == 128) return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+    return ((k >> 3) & 1) << 1;
   } else {
     static_assert(row_bytes == 64 || row_bytes == 128, "B stage rows");
     if constexpr (row_bytes == 128) return ((k >> 1) & 3) | (((k >> 4) & 1) << 2);
@@ -529,11 +541,24 @@ __device__ __forceinline__ void ring_wait(int later) {
   }
 }
 
-constexpr int ring_lds(int tile, int stages) { return stages * 2 * tile * 128; }
+constexpr int ring_lds(int bm, int bn, int stages) { return stages * (bm + bn) * 128; }
+
+// Order a wave's own LDS accesses: its earlier reads have returned before what
+// follows is issued, and the compiler moves none across.
+__device__ __forceinline__ void wave_lds_order() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// gemm_wave_kernel: its tile's columns, a workgroup's waves, and the stages a
+// wave of a tile of bm rows has in flight (what the LDS holds).
+constexpr int kWaveN = 32, kTileWaves = 8;
+constexpr int wave_stages(int bm) { return bm == 16 ? 3 : 2; }
 
 // One work item: the BM x BN tile of C at (m0, n0), K range `slice` of nsplit,
-// on ring_lds bytes of LDS.
-template <int DT, int BM, int BN, int kStages, bool kDma>
+// on ring_lds bytes of LDS.  kWaves = 4: a workgroup's.  kWaves = 1: a single
+// wave's, without barriers; its sums stay in its LDS, kStride bytes per row, for
+// gemm_wave_kernel to add.
+template <int DT, int BM, int BN, int kStages, bool kDma, int kWaves = 4>
 __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned char *__restrict__ A,
                                           const unsigned char *__restrict__ B,
                                           unsigned char *__restrict__ C, int M, int N, int K,
@@ -547,23 +572,29 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
   constexpr int KK = KB / 64;                    // matrix-core K steps per stage
   constexpr int BROW = BN * ES;                  // bytes per B row of a stage
   constexpr int kAStage = BM * KB, kBStage = BN * KB;
-  constexpr int JA = kAStage / 4096, JB = kBStage / 4096;   // 1 KiB pieces per wave
-  constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16;
+  constexpr bool kAlone = kWaves == 1;
+  constexpr int JA = kAStage / 1024 / kWaves, JB = kBStage / 1024 / kWaves;   // 1 KiB pieces per wave
+  constexpr int WTM = kAlone ? BM : BM / 2, WTN = kAlone ? BN : BN / 2;
+  constexpr int FM = WTM / 16, FN = WTN / 16;
+  static_assert(kAlone ? kStages == (kDma ? wave_stages(BM) : 1) : kWaves == 4, "four waves, or one alone");
   static_assert(!kDma || (JA + JB) * (kStages - 2) <= 63, "vmcnt range");
-  static_assert(kDma || kStages == 2, "register-staged: two slots");
+  static_assert(kDma || kAlone || kStages == 2, "register-staged: two slots");
   typedef typename std::conditional<kI8, i32x4, f32x4>::type Acc;
-  static_assert(kStages * (kAStage + kBStage) == ring_lds(BM, kStages), "square tiles");
   unsigned char *const sA = smem;
   unsigned char *const sB = smem + kStages * kAStage;
 
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = kAlone ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int r = lane & 15, g = lane >> 4;
   const int64_t lda_b = lda * ES, ldb_b = ldb * ES, ldc_b = ldc * OB;
   const int nk_all = (K + KE - 1) / KE;
-  const int s_begin = (int)((int64_t)nk_all * slice / nsplit);
-  const int nk = (int)((int64_t)nk_all * (slice + 1) / nsplit) - s_begin;
+  // A range of whole stages, or (alone) every kStep'th: the waves then fetch
+  // adjacent lines, which are spread over the cache's channels.
+  constexpr int kStep = kAlone ? kTileWaves : 1;
+  const int s_begin = kAlone ? slice : (int)((int64_t)nk_all * slice / nsplit);
+  const int nk = kAlone ? (nk_all - slice + kStep - 1) / kStep
+                        : (int)((int64_t)nk_all * (slice + 1) / nsplit) - s_begin;
   const int k_first = s_begin * KE;
 
   // Piece j of a stage: LDS bytes [1024 j, 1024 (j + 1)), lane by lane -- of A
@@ -588,7 +619,8 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
       boff[i] = (unsigned)(b_row(w * JB + i) * ldb_b) + 16u * min(b_chunk(w * JB + i), c_last);
   }
   const unsigned a_lds = lds_addr(sA) + w * JA * 1024, b_lds = lds_addr(sB) + w * JB * 1024;
-  const int tail_t = K - (nk_all - 1) * KE < KE && s_begin + nk == nk_all ? nk - 1 : -1;
+  const bool has_last = s_begin + (nk - 1) * kStep == nk_all - 1;
+  const int tail_t = K - (nk_all - 1) * KE < KE && has_last ? nk - 1 : -1;
   // Addresses of the register loads at stage 0, and for every piece of B the
   // bytes its chunk is shifted by because it crosses N.
   const bool short_rows = K < EPC || N < EPC;
@@ -616,7 +648,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
   };
   // Stage t into registers: whole, or (tail) zeros past K.
   auto get = [&](int t, u32x4 (&ra)[JA], u32x4 (&rb)[JB]) __attribute__((always_inline)) {
-    const int64_t at = (int64_t)t * KB, bt = (int64_t)t * KE * ldb_b;
+    const int64_t at = (int64_t)t * (kStep * KB), bt = (int64_t)t * (kStep * KE) * ldb_b;
     if (t != tail_t && !short_rows) {
 #pragma unroll
       for (int i = 0; i < JA; ++i) ra[i] = load16_any(pa[i] + at);
@@ -624,7 +656,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
       for (int i = 0; i < JB; ++i) rb[i] = load16_any(pb[i] + bt);
       return;
     }
-    const int kleft = K - k_first - t * KE;   // contracted indices left
+    const int kleft = K - k_first - t * (kStep * KE);   // contracted indices left
     if (!short_rows) {
 #pragma unroll
       for (int i = 0; i < JA; ++i) {
@@ -660,8 +692,8 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the stage waits count DMA loads
       return;
     }
-    const unsigned char *ga = abase + (int64_t)t * KB;
-    const unsigned char *gb = bbase + (int64_t)t * KE * ldb_b;
+    const unsigned char *ga = abase + (int64_t)t * (kStep * KB);
+    const unsigned char *gb = bbase + (int64_t)t * (kStep * KE) * ldb_b;
 #pragma unroll
     for (int i = 0; i < JA; ++i) dma_lds16_saddr(ga, aoff[i], a_lds + slot * kAStage + i * 1024);
 #pragma unroll
@@ -695,37 +727,96 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
   for (int a = 0; a < FN; ++a)
 #pragma unroll
     for (int b = 0; b < FM; ++b) acc[a][b] = Acc{0, 0, 0, 0};
-  auto compute = [&](int slot) {
+  auto read_step = [&](int slot, int kk, u32x4 (&xf)[FM], u32x4 (&wf)[FN])
+      __attribute__((always_inline)) {
     const unsigned char *sa = sA + slot * kAStage;
     const unsigned char *sb = sB + slot * kBStage;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      u32x4 xf[FM], wf[FN];
+    for (int fm = 0; fm < FM; ++fm) xf[fm] = *(const u32x4 *)(sa + x_off[kk] + fm * 16 * KB);
 #pragma unroll
-      for (int fm = 0; fm < FM; ++fm) xf[fm] = *(const u32x4 *)(sa + x_off[kk] + fm * 16 * KB);
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn) {
-        u32x2 w0, w1;
-        if constexpr (!kI8) {
-          w0 = lds_read_tr16(sb + w_off[fn] + kk * kWK);
-          w1 = lds_read_tr16(sb + w_off[fn] + kk * kWK + kW1);
-        } else {
-          w0 = lds_read_tr8(sb + w_off[fn] + kk * kWK);
-          w1 = lds_read_tr8(sb + w_off[fn] + kk * kWK + kW1);
-        }
-        wf[fn] = u32x4{w0[0], w0[1], w1[0], w1[1]};
+    for (int fn = 0; fn < FN; ++fn) {
+      u32x2 w0, w1;
+      if constexpr (!kI8) {
+        w0 = lds_read_tr16(sb + w_off[fn] + kk * kWK);
+        w1 = lds_read_tr16(sb + w_off[fn] + kk * kWK + kW1);
+      } else {
+        w0 = lds_read_tr8(sb + w_off[fn] + kk * kWK);
+        w1 = lds_read_tr8(sb + w_off[fn] + kk * kWK + kW1);
       }
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm) {
-          if constexpr (kI8)
-            acc[fn][fm] = mfma_i8_k64(wf[fn], xf[fm], acc[fn][fm]);
-          else
-            acc[fn][fm] = mfma_k32(DT, wf[fn], xf[fm], acc[fn][fm]);
-        }
+      wf[fn] = u32x4{w0[0], w0[1], w1[0], w1[1]};
     }
   };
+  auto multiply = [&](const u32x4 (&xf)[FM], const u32x4 (&wf)[FN]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+      for (int fm = 0; fm < FM; ++fm) {
+        if constexpr (kI8)
+          acc[fn][fm] = mfma_i8_k64(wf[fn], xf[fm], acc[fn][fm]);
+        else
+          acc[fn][fm] = mfma_k32(DT, wf[fn], xf[fm], acc[fn][fm]);
+      }
+  };
+  auto compute = [&](int slot) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      u32x4 xf[FM], wf[FN];
+      read_step(slot, kk, xf, wf);
+      multiply(xf, wf);
+    }
+  };
+
+  constexpr int kStride = WTN * 4 + 16;
+  if constexpr (kAlone) {
+    // A stage's fragments are read into registers, then the stage two later is
+    // fetched in its place under their products: by DMA into the slot, or into
+    // the registers it was written from.
+    u32x4 xf[KK][FM], wf[KK][FN];
+    auto step = [&](int slot, auto fetch) __attribute__((always_inline)) {
+      wave_lds_order();
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) read_step(slot, kk, xf[kk], wf[kk]);
+      wave_lds_order();
+      fetch();
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) multiply(xf[kk], wf[kk]);
+    };
+    if constexpr (kDma) {
+      for (int t = 0; t < kStages; ++t)
+        if (t < nk) issue(t, t);
+      int slot = 0;
+      for (int t = 0; t < nk; ++t) {
+        const int later = nk - 1 - t < kStages - 1 ? nk - 1 - t : kStages - 1;
+        wave_wait<kStages - 1, JA + JB>(later);
+        step(slot, [&]() {
+          if (t + kStages < nk) issue(slot, t + kStages);
+        });
+        slot = slot + 1 == kStages ? 0 : slot + 1;
+      }
+    } else {
+      constexpr int kAhead = wave_stages(BM);
+      u32x4 ra[kAhead][JA], rb[kAhead][JB];
+#pragma unroll
+      for (int h = 0; h < kAhead; ++h)
+        if (h < nk) get(h, ra[h], rb[h]);
+      for (int t = 0; t < nk; t += kAhead) {
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) {
+          if (t + h >= nk) break;
+          put(0, ra[h], rb[h]);
+          step(0, [&]() {
+            if (t + h + kAhead < nk) get(t + h + kAhead, ra[h], rb[h]);
+          });
+        }
+      }
+    }
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+      for (int fm = 0; fm < FM; ++fm)
+        *(Acc *)(smem + (fm * 16 + r) * kStride + (fn * 16 + 4 * g) * 4) = acc[fn][fm];
+    return;
+  }
 
   if constexpr (kDma) {
     for (int s0 = 0; s0 < kStages - 1; ++s0)
@@ -736,7 +827,7 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
       // stay in flight); the barrier makes every wave's share visible and
       // ensures all waves finished reading stage t-1, whose slot is refilled.
       const int later = nk - 1 - t < kStages - 2 ? nk - 1 - t : kStages - 2;
-      ring_wait<kStages - 2, JA + JB>(later);
+      ring_wait<kAlone ? 0 : kStages - 2, JA + JB>(later);
       const int refill = t + kStages - 1;
       if (refill < nk) issue(slot == 0 ? kStages - 1 : slot - 1, refill);
       compute(slot);
@@ -762,9 +853,8 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
 
   // Epilogue: lane holds C[row][col .. col+3] of every accumulator block.
   constexpr bool kSplittable = DT == TCU_F16_F32 || DT == TCU_BF16_F32 || DT == TCU_I8_I32;
-  constexpr int kStride = WTN * 4 + 16;
   unsigned char *stage = smem + w * 32 * kStride;
-  static_assert(4 * 32 * kStride <= kStages * (kAStage + kBStage), "staging fits the ring");
+  static_assert(kAlone || 4 * 32 * kStride <= kStages * (kAStage + kBStage), "staging fits the ring");
   if constexpr (kSplittable) {
     if (nsplit > 1) {
       // Partial tiles are added into C atomically, through this wave's part
@@ -863,7 +953,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
                  unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
                  int64_t ldc, int accum, int tiles_m, int tiles_n, int nsplit, int whole) {
   constexpr int kQuarterStages = kDma ? 4 : 2;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[ring_lds(kTile, kStages)];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[ring_lds(kTile, kTile, kStages)];
   const int tiles = tiles_m * tiles_n;
   // Split items go K range by K range, permuted so that each XCD holds a
   // contiguous run of them (its L2 then serves one range's panels); the
@@ -883,7 +973,7 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   map_tile(pid, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * kTile, n0 = tn * kTile;
   if constexpr (kCut) {
-    static_assert(ring_lds(64, kQuarterStages) <= ring_lds(kTile, kStages), "a quarter's ring");
+    static_assert(ring_lds(64, 64, kQuarterStages) <= ring_lds(kTile, kTile, kStages), "a quarter's ring");
     if (cut) {
       const int mq = m0 + 64 * (quarter >> 1), nq = n0 + 64 * (quarter & 1);
       if (mq < M && nq < N)
@@ -894,6 +984,47 @@ gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__res
   }
   ring_tile<DT, kTile, kTile, kStages, kDma>(smem, A, B, C, M, N, K, lda, ldb, ldc, accum, m0, n0,
                                              slice, kCut ? 1 : nsplit);
+}
+
+// Few tiles, binary32 sums in a fixed order: a workgroup's 8 waves take one tile
+// of kM x 32, each every eighth stage of K, with the stages that fill a CU's LDS in
+// flight; the waves' sums are added in their order, then C's old value.  kM by the
+// tiles: 16 rows while they are one round (192 x 1024 x 320, 120 tiles: 4.6 us, 60 of
+// 32 rows 5.4), else 32 (512 x 1024 x 512, 256 tiles: 6.0, 512 of 16 rows 8.2).
+template <int DT, int kM, bool kDma>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * kTileWaves, 64 * kTileWaves))) void
+gemm_wave_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
+                 unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
+                 int64_t ldc, int accum, int tiles_m, int tiles_n) {
+  static_assert(DT == TCU_F16_F32 || DT == TCU_BF16_F32, "binary32 outputs");
+  constexpr int kStages = kDma ? wave_stages(kM) : 1;
+  constexpr int kPart = ring_lds(kM, kWaveN, kStages), kStride = kWaveN * 4 + 16;
+  static_assert(kM * kStride <= kPart, "a wave's sums");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kTileWaves * kPart];
+  // each XCD holds a contiguous run of tiles
+  int pid = blockIdx.x;
+  const int body = tiles_m * tiles_n / 8 * 8;
+  if (pid < body) pid = (pid % 8) * (body / 8) + pid / 8;
+  int tm, tn;
+  map_tile<64 / kM>(pid, tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * kM, n0 = tn * kWaveN;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  ring_tile<DT, kM, kWaveN, kStages, kDma, 1>(smem + w * kPart, A, B, C, M, N, K, lda, ldb, ldc, 0,
+                                              m0, n0, w, kTileWaves);
+  __syncthreads();
+  const int col = threadIdx.x % kWaveN;
+#pragma unroll
+  for (int i = 0; i < kM; i += 64 * kTileWaves / kWaveN) {
+    const int row = i + threadIdx.x / kWaveN;
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < kTileWaves; ++j)
+      v += *(const float *)(smem + j * kPart + row * kStride + 4 * col);
+    if (m0 + row < M && n0 + col < N) {
+      float *p = (float *)C + (int64_t)(m0 + row) * ldc + n0 + col;
+      *p = accum ? *p + v : v;
+    }
+  }
 }
 
 // Zero the rows x row_words view of 4-byte words at C (row pitch ldc_w
@@ -1019,6 +1150,18 @@ hipError_t launch_ring(const RectArgs &a, int nsplit, int whole, hipStream_t str
   return hipGetLastError();
 }
 
+template <int DT>
+constexpr bool kWaveSums = DT == TCU_F16_F32 || DT == TCU_BF16_F32;
+template <int DT, int kM, bool kDma>
+hipError_t launch_wave(const RectArgs &a, hipStream_t stream) {
+  const int tiles_m = (int)((a.M + kM - 1) / kM), tiles_n = (int)((a.N + kWaveN - 1) / kWaveN);
+  hipLaunchKernelGGL((gemm_wave_kernel<DT, kM, kDma>), dim3(tiles_m * tiles_n),
+                     dim3(64 * kTileWaves), 0, stream, (const unsigned char *)a.A,
+                     (const unsigned char *)a.B, (unsigned char *)a.C, (int)a.M, (int)a.N,
+                     (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
 // Kernel selection by size; the test override TCU_KNOB_GEMM_KERNEL forces
 // the full-tile (ping-pong) kernel wherever its shape conditions hold, the
 // general kernel, or the small-tile ring kernel.
@@ -1048,7 +1191,7 @@ GemmPath gemm_path() {
 // f16 192 x 8192 x 320 (15 tiles of 64) 37 us whole, 10.4 with 16 ranges,
 // 12.9 with 32; bf16 N = 3072 full-tile 74 whole, 135 with 2 ranges.
 // ---------------------------------------------------------------------------
-enum class Tile { kFull, k128, k64 };
+enum class Tile { kFull, k128, k64, kWave32, kWave16 };
 struct Choice {
   Tile tile = Tile::k64;
   int nsplit = 1;
@@ -1084,6 +1227,10 @@ double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool sp
       if (cut) *cut = true;
       return rounds + 0.6 * last;
     }
+    case Tile::kWave32:   // one workgroup per CU, whole rounds
+      return (double)((t + cus - 1) / cus) * (1.9 + (dma ? 0.06 : 0.093) * n64);
+    case Tile::kWave16:
+      return (double)((t + cus - 1) / cus) * (1.7 + (dma ? 0.048 : 0.07) * n64);
     default: {
       // several workgroups per CU; below one per CU the latency of a stage
       const double per_cu = t > cus ? (double)t / (double)cus : 1.0;
@@ -1094,31 +1241,49 @@ double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool sp
 }
 
 void consider(Choice &best, Tile tile, bool dma, int64_t t, int64_t n64, int64_t cus,
-              bool splittable, double split_us, double add_us) {
+              bool ranges, bool tail, double split_us, double add_us) {
   for (int64_t ns = 1;; ns += 1 + ns / 4) {
     // each range keeps at least 512 bytes of the contracted index
-    if (ns > 1 && (!splittable || n64 / ns < 8 || t * ns > 3 * cus)) break;
+    if (ns > 1 && (!ranges || n64 / ns < 8 || t * ns > 3 * cus)) break;
     double us = model_us(tile, dma, t * ns, (double)((n64 + ns - 1) / ns), cus,
-                         splittable && ns == 1);
+                         tail && ns == 1);
     if (ns > 1) us += split_us + add_us * (double)ns;
     if (us < best.us) best = Choice{tile, (int)ns, us};
   }
 }
 
+// Whether K may be cut into ranges added atomically.  int32 sums are the same
+// in any order; a binary32 sum is not, and is cut only from kRangesK on (as by
+// tail_split, whose ranges keep as many stages): below it every product repeats
+// bit for bit.  us, K in order (gemm_wave_kernel) / in ranges, f16 accumulating,
+// operands not in the caches: 128 x 1024 x 128 4.4 / 4.6, 300 x 1024 x 300 at an odd
+// pitch 5.7 / 6.3, 16 x 1536 x 1024 5.8 / 4.2, 192 x 2048 x 320 6.2 / 5.3, 192 x 8192
+// x 320 15.8 / 9.1; whole on 64 x 64 tiles 192 x 1024 x 320 8.0, 2048 12.0.
+constexpr int64_t kRangesK = 2 * kMinSplitStages * (kFastKB / 2);   // 2048
+template <int DT>
+constexpr bool ranges_ok(int64_t K) {
+  return DT == TCU_I8_I32 || (DT != TCU_BF16_BF16 && K >= kRangesK);
+}
+
 // The ring kernel: tile and split by the model.
 template <int DT>
-Choice choose_ring(const RectArgs &a, bool dma, bool small_only, int64_t cus) {
+Choice choose_ring(const RectArgs &a, bool dma, GemmPath path, int64_t cus) {
   constexpr int ES = in_bytes(DT);
   const int64_t n64 = (a.K * ES + 63) / 64;
   const double mn = (double)a.M * (double)a.N;
   const double split_us = 1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), add_us = mn / 1.2e6;
   Choice c;
-  constexpr bool kSplit = DT != TCU_BF16_BF16;
-  consider(c, Tile::k64, dma, ((a.M + 63) / 64) * ((a.N + 63) / 64), n64, cus, kSplit, split_us,
-           add_us);
-  if (!small_only)
-    consider(c, Tile::k128, dma, ((a.M + 127) / 128) * ((a.N + 127) / 128), n64, cus, kSplit,
-             split_us, add_us);
+  const bool ranges = ranges_ok<DT>(a.K);
+  consider(c, Tile::k64, dma, ((a.M + 63) / 64) * ((a.N + 63) / 64), n64, cus, ranges, false,
+           split_us, add_us);
+  if (path == GemmPath::kRing) return c;
+  consider(c, Tile::k128, dma, ((a.M + 127) / 128) * ((a.N + 127) / 128), n64, cus, ranges, false,
+           split_us, add_us);
+  if (kWaveSums<DT> && !ranges && path != GemmPath::kGeneral) {
+    const int64_t tn = (a.N + kWaveN - 1) / kWaveN;
+    consider(c, Tile::kWave32, dma, (a.M + 31) / 32 * tn, n64, cus, false, false, 0, 0);
+    consider(c, Tile::kWave16, dma, (a.M + 15) / 16 * tn, n64, cus, false, false, 0, 0);
+  }
   return c;
 }
 
@@ -1150,6 +1315,12 @@ hipError_t launch_ring_choice(const RectArgs &a, bool dma, const Choice &c, hipS
     return dma ? launch_ring<DT, 128, true>(a, ns, whole, stream, num_cus)
                : launch_ring<DT, 128, false>(a, ns, whole, stream, num_cus);
   }
+  if constexpr (kWaveSums<DT>) {
+    if (c.tile == Tile::kWave32 && forced <= 0)
+      return dma ? launch_wave<DT, 32, true>(a, stream) : launch_wave<DT, 32, false>(a, stream);
+    if (c.tile == Tile::kWave16 && forced <= 0)
+      return dma ? launch_wave<DT, 16, true>(a, stream) : launch_wave<DT, 16, false>(a, stream);
+  }
   return dma ? launch_ring<DT, 64, true>(a, ns, INT_MAX, stream, num_cus)
              : launch_ring<DT, 64, false>(a, ns, INT_MAX, stream, num_cus);
 }
@@ -1158,7 +1329,7 @@ template <int DT>
 hipError_t launch_general(const RectArgs &a, GemmPath path, hipStream_t stream, int num_cus,
                           int64_t cus) {
   const bool dma = path != GemmPath::kGeneral && ring_dma_ok<DT>(a);
-  return launch_ring_choice<DT>(a, dma, choose_ring<DT>(a, dma, path == GemmPath::kRing, cus),
+  return launch_ring_choice<DT>(a, dma, choose_ring<DT>(a, dma, path, cus),
                                 stream, num_cus, cus);
 }
 
@@ -1182,7 +1353,7 @@ hipError_t launch_full(const RectArgs &a, int tm, int tn, int nsplit, hipStream_
       if (e != hipSuccess) return e;
     }
   } else {
-    nsplit = tail_split<DT>(tiles, want < tiles ? want : tiles, (a.K + KE - 1) / KE, &full);
+    nsplit = tail_split<DT>(tiles, want < tiles ? want : tiles, a.K / KE, &full);
     if (nsplit > 1 && !a.accum) {
       // clipped to this launch's part of C
       const int64_t rows = a.M < 256 * (int64_t)tm ? a.M : 256 * (int64_t)tm;
@@ -1236,7 +1407,7 @@ hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
     return launch_full<DT, false>(a, tm, tn, (int)ns, stream, num_cus);
   }
   const bool dma = ring_dma_ok<DT>(a);
-  Choice best = choose_ring<DT>(a, dma, false, cus);
+  Choice best = choose_ring<DT>(a, dma, path, cus);
   const int64_t M0 = a.M / 256 * 256, N0 = a.N / 256 * 256;
   const bool edges_in_kernel = (a.N * ES) % 16 == 0;
   const int64_t tm = edges_in_kernel ? (a.M + 255) / 256 : M0 / 256;
@@ -1245,16 +1416,16 @@ hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
     Choice full;
     const double mn = (double)a.M * (double)a.N;
     // A split is taken on whole tiles only.
-    consider(full, Tile::kFull, true, tm * tn, n64, cus, kSplit && whole,
-             1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), mn / 1.2e6);
+    consider(full, Tile::kFull, true, tm * tn, n64, cus, whole && ranges_ok<DT>(a.K),
+             kSplit && whole, 1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), mn / 1.2e6);
     if (!edges_in_kernel) {
       // the strips, one launch each
       RectArgs b = a, r = a;
       b.M = a.M - M0;
       r.M = M0;
       r.N = a.N - N0;
-      if (b.M > 0) full.us += 3 + choose_ring<DT>(b, false, false, cus).us;
-      if (r.N > 0) full.us += 3 + choose_ring<DT>(r, false, false, cus).us;
+      if (b.M > 0) full.us += 3 + choose_ring<DT>(b, false, path, cus).us;
+      if (r.N > 0) full.us += 3 + choose_ring<DT>(r, false, path, cus).us;
     }
     if (full.us < best.us) best = full;
   }
