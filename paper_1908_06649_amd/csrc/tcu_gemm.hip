@@ -1186,6 +1186,15 @@ GemmPath gemm_path() {
 //   int8 N = 1536: 28 / 13.7 / 13.6    N = 2560: 39 / 26 / 41
 //        N = 3072: 44 / 47 / 74        N = 4096: 64 / 73 / 190
 // (N = 3072's last round of 64 tiles whole; in quarters int8 takes 41.)
+//   M x K x N full / 128, operands not in the caches:
+//   f16  4350 x 4096 x 4352 (last round of 33 tiles split) 166 / 189
+//        6000 x 1000 x 6000 116 / 125   6000 x 6000 x 6000 395 / 571
+//        7000 x 1024 x 7008 128 / 148   4350 x 1024 x 4352 77 / 65
+//   bf16 out 6000 x 512 x 6000 57 / 61  4350 x 4096 x 4352 208 / 186
+// Fitted to 170 such sizes of 100 to 2500 full tiles: the full-tile kernel within 6
+// %, 128 x 128 within 7 %; the choice is 0.4 % from the better one on average, and
+// up to 16 % (7000 x 1024 x 7008, whose last round is 16 full tiles).  Rows of A or B that start inside a 128-byte line cost
+// the smaller tiles, which fetch whole lines, more than the full ones.
 // Filled through registers the ring kernel takes 1.1 to 1.25 times as long.
 // Split ranges are added atomically, after zeroing C when overwriting:
 // f16 192 x 8192 x 320 (15 tiles of 64) 37 us whole, 10.4 with 16 ranges,
@@ -1198,34 +1207,51 @@ struct Choice {
   double us = 1e30;
 };
 
+// What a product's time depends on besides its tiles: whether the ring kernel
+// fills by DMA, the bytes of an output, and the rows that start inside a line.
+struct Traits {
+  bool dma;
+  int ob;
+  bool a_inside, b_inside;
+};
+template <int DT>
+Traits traits(const RectArgs &a, bool dma) {
+  constexpr int ES = in_bytes(DT);
+  return Traits{dma, out_bytes(DT), a.lda * ES % 128 != 0, a.ldb * ES % 128 != 0};
+}
+
 // *cut: whether the tiles of a last, partial round are cut into quarters (128).
-double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool splittable,
+double model_us(Tile tile, const Traits &f, int64_t t, double n64, int64_t cus, bool splittable,
                 bool *cut = nullptr) {
+  const bool dma = f.dma;
   switch (tile) {
     case Tile::kFull: {
       // one workgroup per CU, whole rounds; the last may be split
-      const double round = 0.72 * n64 + 8;
+      const double stages = 0.7 * n64 * (1 + 0.07 * (f.a_inside + f.b_inside));
+      const double round = stages + 8 + 1.7 * f.ob * (t < cus ? (double)t / (double)cus : 1.0);
       const int ns = splittable ? tail_ranges(t, cus, (int64_t)n64) : 1;
-      if (ns > 1) return (double)(t / cus) * round + 0.72 * n64 / ns + 12;
+      if (ns > 1) return (double)(t / cus) * round + stages / ns + 33;
       return (double)((t + cus - 1) / cus) * round;
     }
     case Tile::k128: {
       // two workgroups per CU, which share its LDS bandwidth
-      const double pair = 0.44 * n64 + 5, single = 0.33 * n64 + 4;
-      const int64_t rem = t % (2 * cus);
-      const double rounds = (double)(t / (2 * cus)) * pair * (dma ? 1.0 : 1.22);
-      const double last = (rem > cus ? pair : rem > 0 ? single : 0.0) * (dma ? 1.0 : 1.22);
       if (cut) *cut = false;
-      if (t < 2 * cus || rem == 0) return rounds + last;
+      if (t < 2 * cus) return (t > cus ? 0.44 * n64 + 5 : 0.33 * n64 + 4) * (dma ? 1.0 : 1.22);
+      const double fill = dma ? 1 + 0.22 * f.a_inside + 0.1 * f.b_inside : 1.22;
+      const double pair = 0.46 * n64 * fill + 4 + f.ob, single = 0.35 * n64 * fill + 4.5;
+      const int64_t rem = t % (2 * cus);
+      const double rounds = (double)(t / (2 * cus)) * pair;
+      const double last = rem > cus ? pair : rem > 0 ? single : 0.0;
+      if (rem == 0) return rounds;
       // The tiles of a last round of at most cus / 2 are cut into quarters, two
-      // per CU at most, which take about 0.6 of a tile's time (us, whole / cut;
+      // per CU at most, which take about 0.55 of a tile's time (us, whole / cut;
       // odd pitches, bf16: 3072 x 1000 x 3071, 64 tiles, 45.9 / 40.2; 3200 x
       // 1000 x 3199, 113 tiles, 45.7 / 42.9; 3328 x 1000 x 3327, 164 tiles,
       // 46.1 / 50.7; by DMA 3072 x 2048 x 3072, 64 tiles, 56.7 / 46.7; 3200 x
       // 512 x 3200, 113 tiles, 23.9 / 21.5; 3328 x 1024 x 3328 35.3 / 36.2).
       if (2 * rem > cus) return rounds + last;
       if (cut) *cut = true;
-      return rounds + 0.6 * last;
+      return rounds + 0.55 * last;
     }
     case Tile::kWave32:   // one workgroup per CU, whole rounds
       return (double)((t + cus - 1) / cus) * (1.9 + (dma ? 0.06 : 0.093) * n64);
@@ -1240,12 +1266,12 @@ double model_us(Tile tile, bool dma, int64_t t, double n64, int64_t cus, bool sp
   }
 }
 
-void consider(Choice &best, Tile tile, bool dma, int64_t t, int64_t n64, int64_t cus,
+void consider(Choice &best, Tile tile, const Traits &f, int64_t t, int64_t n64, int64_t cus,
               bool ranges, bool tail, double split_us, double add_us) {
   for (int64_t ns = 1;; ns += 1 + ns / 4) {
     // each range keeps at least 512 bytes of the contracted index
     if (ns > 1 && (!ranges || n64 / ns < 8 || t * ns > 3 * cus)) break;
-    double us = model_us(tile, dma, t * ns, (double)((n64 + ns - 1) / ns), cus,
+    double us = model_us(tile, f, t * ns, (double)((n64 + ns - 1) / ns), cus,
                          tail && ns == 1);
     if (ns > 1) us += split_us + add_us * (double)ns;
     if (us < best.us) best = Choice{tile, (int)ns, us};
@@ -1274,15 +1300,16 @@ Choice choose_ring(const RectArgs &a, bool dma, GemmPath path, int64_t cus) {
   const double split_us = 1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), add_us = mn / 1.2e6;
   Choice c;
   const bool ranges = ranges_ok<DT>(a.K);
-  consider(c, Tile::k64, dma, ((a.M + 63) / 64) * ((a.N + 63) / 64), n64, cus, ranges, false,
+  const Traits f = traits<DT>(a, dma);
+  consider(c, Tile::k64, f, ((a.M + 63) / 64) * ((a.N + 63) / 64), n64, cus, ranges, false,
            split_us, add_us);
   if (path == GemmPath::kRing) return c;
-  consider(c, Tile::k128, dma, ((a.M + 127) / 128) * ((a.N + 127) / 128), n64, cus, ranges, false,
+  consider(c, Tile::k128, f, ((a.M + 127) / 128) * ((a.N + 127) / 128), n64, cus, ranges, false,
            split_us, add_us);
   if (kWaveSums<DT> && !ranges && path != GemmPath::kGeneral) {
     const int64_t tn = (a.N + kWaveN - 1) / kWaveN;
-    consider(c, Tile::kWave32, dma, (a.M + 31) / 32 * tn, n64, cus, false, false, 0, 0);
-    consider(c, Tile::kWave16, dma, (a.M + 15) / 16 * tn, n64, cus, false, false, 0, 0);
+    consider(c, Tile::kWave32, f, (a.M + 31) / 32 * tn, n64, cus, false, false, 0, 0);
+    consider(c, Tile::kWave16, f, (a.M + 15) / 16 * tn, n64, cus, false, false, 0, 0);
   }
   return c;
 }
@@ -1310,7 +1337,7 @@ hipError_t launch_ring_choice(const RectArgs &a, bool dma, const Choice &c, hipS
     const int64_t t = ((a.M + 127) / 128) * ((a.N + 127) / 128);
     const int64_t n64 = (a.K * in_bytes(DT) + 63) / 64;
     bool cut = false;
-    model_us(Tile::k128, dma, t, (double)n64, cus, false, &cut);
+    model_us(Tile::k128, traits<DT>(a, dma), t, (double)n64, cus, false, &cut);
     const int whole = (int)(cut ? t - t % (2 * cus) : t);
     return dma ? launch_ring<DT, 128, true>(a, ns, whole, stream, num_cus)
                : launch_ring<DT, 128, false>(a, ns, whole, stream, num_cus);
@@ -1415,9 +1442,10 @@ hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
   if (vec && a.K >= KE && tm >= 1 && tn >= 1) {
     Choice full;
     const double mn = (double)a.M * (double)a.N;
-    // A split is taken on whole tiles only.
-    consider(full, Tile::kFull, true, tm * tn, n64, cus, whole && ranges_ok<DT>(a.K),
-             kSplit && whole, 1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), mn / 1.2e6);
+    // Ranges of every tile are taken on whole tiles only, of a last round's
+    // tiles on any shape (as launch_full does).
+    consider(full, Tile::kFull, traits<DT>(a, true), tm * tn, n64, cus,
+             whole && ranges_ok<DT>(a.K), kSplit && a.K / KE >= 2 * kMinSplitStages, 1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), mn / 1.2e6);
     if (!edges_in_kernel) {
       // the strips, one launch each
       RectArgs b = a, r = a;
