@@ -23,7 +23,8 @@
 // own twiddle does and nothing on the last level, where J' = 0.
 //
 // One launch holds as many levels as it can:
-//   * vectors of up to 2^13 elements: all of them, in LDS (dft_local_kernel);
+//   * vectors of up to 2^13 elements: all of them, in LDS (dft_local_kernel;
+//     few long ones in more launches, see local_fits);
 //   * else pairs of full-radix levels, through LDS (dft_pair_kernel), and
 //     single levels (dft_level_kernel).
 // Every kernel forms a value by the same operations, so the results do not
@@ -877,6 +878,17 @@ hipError_t launch_local(const f32x2 *src, f32x2 *dst, int64_t n, int64_t batch,
   return launch_local_t<S, 13>(src, dst, n, batch, stream, num_cus);
 }
 
+// Whether whole vectors per workgroup are the faster division: up to 2^13
+// elements, except few long vectors with s = 16, whose three or four levels in one
+// workgroup each take longer than the launches that spread them over the chip
+// (us, whole / divided: n = 2^13, batch 1 13.1 / 10.3, 32 14.2 / 12.4, 64 14.4 / 14.9;
+// n = 2^12, 1 7.6 / 6.7, 32 8.3 / 7.4, 64 8.2 / 8.1, 128 8.3 / 9.4; s = 32, n = 2^13,
+// 1 10.7 / 11.8).
+bool local_fits(int64_t n, int64_t batch, int s, int num_cus) {
+  if (n > (int64_t)1 << kLocalLg || knob(TCU_KNOB_DFT_PAIRS) == 1) return false;
+  return !(s == 16 && n >= 1 << 12 && 4 * batch < num_cus);
+}
+
 constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxScratchDevices] = {};
@@ -911,7 +923,7 @@ int dft_levels(int64_t n, int s) {
 hipError_t launch_dft(const void *x, void *y, void *work, int64_t n, int64_t batch, int s,
                       hipStream_t stream, int num_cus) {
   if (n <= 0 || batch <= 0) return hipSuccess;
-  if (n <= (1 << kLocalLg) && knob(TCU_KNOB_DFT_PAIRS) != 1)
+  if (local_fits(n, batch, s, num_cus))
     return s == 32 ? launch_local<32>((const f32x2 *)x, (f32x2 *)y, n, batch, stream, num_cus)
                    : launch_local<16>((const f32x2 *)x, (f32x2 *)y, n, batch, stream, num_cus);
   const int L = dft_levels(n, s);

@@ -46,3 +46,16 @@ def test_tile_choice(so, M, K, N, dtype, want):
     names = kernels(rec.run(so, [rec.product(M, K, N, dtype)])[0])
     part = {"ring128": f"gemm_ring_kernelILi{dtype}ELi128", "ring64": f"gemm_ring_kernelILi{dtype}ELi64"}
     assert any(part.get(want, want) in n for n in names), names
+
+
+# Few long vectors with s = 16 are faster divided among launches (2^12: a pair
+# and a level; 2^13: a pair and two levels), more of them, shorter ones and s = 32
+# whole in one.
+@pytest.mark.parametrize("n,batch,s,launches", [
+    (1 << 13, 1, 16, 3), (1 << 13, 63, 16, 3), (1 << 13, 64, 16, 1), (1 << 12, 4, 16, 2),
+    (1 << 12, 64, 16, 1), (1 << 11, 1, 16, 1), (1 << 13, 1, 32, 1), (1, 7, 32, 1)])
+def test_dft_division(so, n, batch, s, launches):
+    job = dict(fn="tcu_dft_ex", args=[rec.ptr(0), rec.ptr(1), rec.ptr(2), n, batch, s, None])
+    names = kernels(rec.run(so, [job])[0])
+    assert len(names) == launches, names
+    assert (launches == 1) == names[0].startswith("dft_local")
