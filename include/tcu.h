@@ -366,8 +366,9 @@ const char *tcu_strerror(int status);
  * choice.  Products never read the environment; only the initial value of
  * TCU_KNOB_CHECK_POINTERS comes from TCU_DEBUG at load time.
  *   TCU_KNOB_GEMM_KERNEL: TCU_PATH_AUTO, TCU_PATH_FULL_TILE (the 256 x 256
- *     persistent kernel wherever its whole-tile conditions hold),
- *     TCU_PATH_GENERAL (the ring kernel filled through registers),
+ *     persistent kernel wherever its conditions hold: rows at multiples of 16
+ *     bytes and a stage of K; ragged edges in the kernel or around its
+ *     interior), TCU_PATH_GENERAL (the ring kernel filled through registers),
  *     TCU_PATH_RING (the ring kernel's 64 x 64 tiles, filled by direct loads
  *     where its shape conditions hold).
  *   TCU_KNOB_PP_GRID: workgroups of the persistent full-tile kernel, and the

@@ -1162,9 +1162,9 @@ hipError_t launch_wave(const RectArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Kernel selection by size; the test override TCU_KNOB_GEMM_KERNEL forces
-// the full-tile (ping-pong) kernel wherever its shape conditions hold, the
-// general kernel, or the small-tile ring kernel.
+// Kernel selection by size; the test override TCU_KNOB_GEMM_KERNEL forces the
+// full-tile (ping-pong) kernel wherever its shape conditions hold (ragged
+// shapes too), the ring kernel filled through registers, or its 64 x 64 tiles.
 enum class GemmPath { kAuto, kFast, kGeneral, kRing };
 GemmPath gemm_path() {
   switch (knob(TCU_KNOB_GEMM_KERNEL)) {
@@ -1445,7 +1445,8 @@ hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
     // Ranges of every tile are taken on whole tiles only, of a last round's
     // tiles on any shape (as launch_full does).
     consider(full, Tile::kFull, traits<DT>(a, true), tm * tn, n64, cus,
-             whole && ranges_ok<DT>(a.K), kSplit && a.K / KE >= 2 * kMinSplitStages, 1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), mn / 1.2e6);
+             whole && ranges_ok<DT>(a.K), kSplit && a.K / KE >= 2 * kMinSplitStages,
+             1.5 + (a.accum ? 0.0 : 2.5 + mn * 4e-6), mn / 1.2e6);
     if (!edges_in_kernel) {
       // the strips, one launch each
       RectArgs b = a, r = a;
@@ -1455,7 +1456,7 @@ hipError_t launch_dt(const RectArgs &a, hipStream_t stream, int num_cus) {
       if (b.M > 0) full.us += 3 + choose_ring<DT>(b, false, path, cus).us;
       if (r.N > 0) full.us += 3 + choose_ring<DT>(r, false, path, cus).us;
     }
-    if (full.us < best.us) best = full;
+    if (full.us < best.us || path == GemmPath::kFast) best = full;
   }
   if (best.tile != Tile::kFull) return launch_ring_choice<DT>(a, dma, best, stream, num_cus, cus);
   if (whole)

@@ -59,3 +59,90 @@ def test_dft_division(so, n, batch, s, launches):
     names = kernels(rec.run(so, [job])[0])
     assert len(names) == launches, names
     assert (launches == 1) == names[0].startswith("dft_local")
+
+
+def aligned(cols, dtype_bytes, extra):
+    """The padded pitches of the GPU tests."""
+    step = 16 // dtype_bytes
+    return (cols + step - 1) // step * step + extra * step
+
+
+def padded(M, K, N, dtype, knobs, acc=False):
+    es, ob = (1 if dtype == I8 else 2), (2 if dtype == BF16OUT else 4)
+    return rec.product(M, K, N, dtype, lda=aligned(K, es, 1), ldb=aligned(N, es, 2),
+                       ldc=aligned(N, ob, 1), acc=acc, knobs=knobs)
+
+
+def test_forced_full_tiles_on_ragged_shapes(so):
+    """What tests/test_full_ragged_gpu.py names is what it runs."""
+    import test_full_ragged_gpu as t
+    for dtype in (F16, BF16, BF16OUT, I8):
+        for shapes, strips in ((t.EDGES, False), (t.STRIPS, True)):
+            for M, K, N in shapes:
+                if dtype == I8 and (N % 16 != 0) != strips:
+                    continue
+                knobs = [(tcu.TCU_KNOB_GEMM_KERNEL, tcu.TCU_PATH_FULL_TILE),
+                         (tcu.TCU_KNOB_PP_GRID, 2), (tcu.TCU_KNOB_TAIL_SPLIT, 1)]
+                names = kernels(rec.run(so, [padded(M, K, N, dtype, knobs)])[0])
+                whole = M % 256 == 0 and N % 256 == 0 and K % (64 if dtype == I8 else 32) == 0
+                assert names[0] == f"gemm_pp_kernelILi{dtype}ELi5ELb{int(not whole)}E", names
+                assert (len(names) > 1) == strips, names
+    for M, K, N, grid in ((700, 1030, 656, 8), (700, 1030, 784, 5), (800, 1001, 777, 4)):
+        knobs = [(tcu.TCU_KNOB_GEMM_KERNEL, tcu.TCU_PATH_FULL_TILE), (tcu.TCU_KNOB_PP_GRID, grid),
+                 (tcu.TCU_KNOB_TAIL_SPLIT, 3)]
+        names = kernels(rec.run(so, [padded(M, K, N, F16, knobs)])[0])
+        assert names[0].startswith("zero_tiles") and names[1].startswith("gemm_pp"), names
+
+
+def test_quarters_are_taken(so):
+    """The shapes of tests/test_ring_gpu.py's quarters cut a last round."""
+    import test_ring_gpu as t
+    shapes = [m.args[1] for m in t.test_ring_quarters.pytestmark
+              if m.name == "parametrize" and m.args[0] == "M,K,N"][0]
+    jobs = [padded(M, K, N, d, [(tcu.TCU_KNOB_PP_GRID, 2)]) for M, K, N in shapes
+            for d in (F16, BF16, BF16OUT, I8)]
+    for answer in rec.run(so, jobs):
+        names = kernels(answer)
+        assert "ELi128ELi2ELb" in names[0] and names[0].endswith("ELb1E"), names
+
+
+def test_shared_k_is_taken(so):
+    """The shapes of tests/test_product_order_gpu.py take the tile of the height
+    they name, except the ones of at most two stages."""
+    import test_product_order_gpu as t
+    shapes = [m.args[1] for m in t.test_shared_k_edges.pytestmark
+              if m.name == "parametrize" and m.args[0] == "M,K,N"][0]
+    for M, K, N in shapes:
+        for height in (16, 32):
+            tiles = -(-M // height) * -(-N // 32)
+            name = kernels(rec.run(so, [padded(M, K, N, BF16, [(tcu.TCU_KNOB_PP_GRID, tiles)])])[0])[0]
+            if K > 128 and (height == 16 or M > 16):
+                assert name.startswith(f"gemm_wave_kernelILi{BF16}ELi{height}E"), (M, K, N, name)
+
+
+def test_binary32_repeats_below_2048(so):
+    """No binary32 product with K below 2048 is cut into ranges, whatever its
+    sizes, pitches and type, and some from 2048 on are."""
+    rng = random.Random(5)
+    arity = [("gemm_ring", 14), ("gemm_pp", 12)]
+
+    def ranges(K, acc):
+        M, N = (max(1, int(2 ** rng.uniform(0, 13.2))) for _ in range(2))
+        if rng.random() < 0.5:
+            M, N = max(256, M // 256 * 256), max(256, N // 256 * 256)
+        pad = rng.choice([0, 0, 8, 1])
+        return rec.product(M, K, N, rng.choice([F16, BF16]), lda=K + pad, ldb=N + pad, ldc=N + pad,
+                           acc=acc, arity=arity)
+
+    def cut(answer):
+        return any(la["name"].find("zero_") >= 0
+                   or (la["name"].find("gemm_ring") >= 0 and la["ints"][12] > 1)
+                   or (la["name"].find("gemm_pp") >= 0 and la["ints"][11] > 1)
+                   for la in answer["launches"])
+
+    below = [ranges(rng.choice([2047, 2016, int(2 ** rng.uniform(0, 11))]), rng.random() < 0.5)
+             for _ in range(1500)]
+    answers = rec.run(so, below)
+    assert not any(cut(a) for a in answers)
+    assert any(a["launches"][0]["name"].find("gemm_pp") >= 0 for a in answers)
+    assert sum(cut(a) for a in rec.run(so, [ranges(4096, True) for _ in range(200)])) > 20

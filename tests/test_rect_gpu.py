@@ -98,18 +98,11 @@ def test_rect_ring_kernel(M, K, N, din, out, accumulate, pitch, knobs):
     run_and_check(M, K, N, din, out, s, pitch, accumulate, seed=M + 5 * K + 11 * N)
 
 
-# Large ragged shapes (at least one 256 x 256 tile per CU): the full-tile
-# kernel with the contracted index's partial last stage zero-padded in the
-# kernel, and either its own edge tiles (N a whole number of 16-byte chunks)
-# or the general kernel for the bottom rows and right columns.  All three
-# dimensions ragged with edges in the kernel (4176: also for int8) or in
-# strips (4173); edges in the kernel for 16-bit inputs and in strips for
-# int8 (4104); only K; only M; a K tail of one element with one ragged
-# column (int8: K below one stage, the general kernel alone).  Contiguous
-# pitches that are not multiples of 16 bytes take the general kernel with
-# 128 x 128 tiles, whole chunks loaded in 8-byte pieces (int8 K = 1000,
-# bfloat16 N = 4100), 4-byte pieces (int8 K = 1004) or element by element
-# (odd int8 or 16-bit pitches).
+# Large ragged shapes, as the size chooses: the full-tile kernel with its edges
+# inside (4096 x 1000 x 4096 and 4100 x 1024 x 4096 with 16-bit inputs), else 128 x 128
+# ring tiles, the last round whole or in quarters, by DMA (4176, 4104) or through
+# registers (4173, 4097, and pitches that are no multiple of 16 bytes: int8
+# K = 1000 and 1004, bfloat16 N = 4100, odd ones).
 LARGE_RAGGED = [(4101, 1000, 4176), (4101, 1000, 4173), (4375, 1000, 4104), (4096, 1000, 4096),
                 (4100, 1024, 4096), (4096, 33, 4097), (4101, 1004, 4100)]
 
@@ -195,13 +188,14 @@ def test_rect_tail_split_chosen_by_size(din, out, knobs):
 @pytest.mark.parametrize("din,out", PAIRS)
 @pytest.mark.parametrize("M,K,N", [(4101, 1000, 4176), (4375, 1000, 4104)])
 def test_rect_large_ragged_tail_split(M, K, N, din, out, accumulate, knobs):
-    """The ragged full-tile kernel with its tail tiles split 3 ways: edge
-    tiles in the kernel (17 x 17 tiles) and, for int8 on the second shape,
-    the 256-aligned interior (17 x 16 tiles) with the general kernel on the
+    """The ragged full-tile kernel, forced, with its tail tiles split 3 ways: edge
+    tiles in the kernel (17 x 17 and 18 x 17 tiles) and, for int8 on the second
+    shape, the 256-aligned interior (17 x 16 tiles) with the ring kernel on the
     strips."""
+    knobs(tcu.TCU_KNOB_GEMM_KERNEL, tcu.TCU_PATH_FULL_TILE)
     knobs(tcu.TCU_KNOB_TAIL_SPLIT, 3)
     s = 32 if din == "bf16" else 16
-    run_and_check(M, K, N, din, out, s, "contiguous", accumulate, seed=M + K + N + 1)
+    run_and_check(M, K, N, din, out, s, "padded", accumulate, seed=M + K + N + 1)
 
 
 @pytest.mark.parametrize("s", [16, 32])
