@@ -951,14 +951,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(256, 256),
                           amdgpu_waves_per_eu(1, kTile == 64 ? (kDma ? 3 : 4) : 2))) void
 gemm_ring_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ B,
                  unsigned char *__restrict__ C, int M, int N, int K, int64_t lda, int64_t ldb,
-                 int64_t ldc, int accum, int tiles_m, int tiles_n, int nsplit, int whole) {
+                 int64_t ldc, int accum, int tiles_m, int tiles_n, int nsplit, int whole,
+                 int first) {
   constexpr int kQuarterStages = kDma ? 4 : 2;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[ring_lds(kTile, kTile, kStages)];
   const int tiles = tiles_m * tiles_n;
   // Split items go K range by K range, permuted so that each XCD holds a
   // contiguous run of them (its L2 then serves one range's panels); the
   // items past the last multiple of 8 keep their ids.
-  int pid = blockIdx.x, slice = 0, quarter = 0;
+  int pid = first + blockIdx.x, slice = 0, quarter = 0;
   const bool cut = kCut && pid >= whole;
   if (!kCut && nsplit > 1) {
     const int body = tiles * nsplit / 8 * 8;
@@ -1137,11 +1138,16 @@ hipError_t launch_ring(const RectArgs &a, int nsplit, int whole, hipStream_t str
   const int tiles = tiles_m * tiles_n;
   if (whole > tiles || nsplit > 1) whole = tiles;
   auto go = [&](auto cut, int items) {
-    hipLaunchKernelGGL((gemm_ring_kernel<DT, kTile, kStages, kDma, decltype(cut)::value>),
-                       dim3(items), dim3(256), 0, stream, (const unsigned char *)a.A,
-                       (const unsigned char *)a.B, (unsigned char *)a.C, (int)a.M, (int)a.N,
-                       (int)a.K, a.lda, a.ldb, a.ldc, a.accum ? 1 : 0, tiles_m, tiles_n, nsplit,
-                       whole);
+    // A launch's work items count in 32 bits (2^30 rows of one column are 2^24
+    // tiles of 64 x 64): more workgroups than that take several launches.
+    constexpr int kMost = 1 << 23;
+    for (int first = 0; first < items && (first == 0 || hipPeekAtLastError() == hipSuccess);
+         first += kMost)
+      hipLaunchKernelGGL((gemm_ring_kernel<DT, kTile, kStages, kDma, decltype(cut)::value>),
+                         dim3(items - first < kMost ? items - first : kMost), dim3(256), 0, stream,
+                         (const unsigned char *)a.A, (const unsigned char *)a.B,
+                         (unsigned char *)a.C, (int)a.M, (int)a.N, (int)a.K, a.lda, a.ldb, a.ldc,
+                         a.accum ? 1 : 0, tiles_m, tiles_n, nsplit, whole, first);
   };
   if (kTile == 128 && whole < tiles)
     go(std::integral_constant<bool, kTile == 128>{}, whole + 4 * (tiles - whole));

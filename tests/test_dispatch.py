@@ -124,7 +124,7 @@ def test_binary32_repeats_below_2048(so):
     """No binary32 product with K below 2048 is cut into ranges, whatever its
     sizes, pitches and type, and some from 2048 on are."""
     rng = random.Random(5)
-    arity = [("gemm_ring", 14), ("gemm_pp", 12)]
+    arity = [("gemm_ring", 15), ("gemm_pp", 12)]
 
     def ranges(K, acc):
         M, N = (max(1, int(2 ** rng.uniform(0, 13.2))) for _ in range(2))
@@ -146,3 +146,22 @@ def test_binary32_repeats_below_2048(so):
     assert not any(cut(a) for a in answers)
     assert any(a["launches"][0]["name"].find("gemm_pp") >= 0 for a in answers)
     assert sum(cut(a) for a in rec.run(so, [ranges(4096, True) for _ in range(200)])) > 20
+
+
+@pytest.mark.parametrize("M,K,N,dtype", [(1 << 30, 8, 1, BF16), ((1 << 30) - 63, 3, 5, F16),
+                                         (1 << 30, 1, 129, BF16OUT), (5, 8, 1 << 30, I8),
+                                         (1 << 29, 40, 16, F16)])
+def test_largest_dimensions(so, M, K, N, dtype):
+    """Products whose tiles exceed a launch's 32-bit count of work items are
+    accepted and every tile is taken once."""
+    answer = rec.run(so, [rec.product(M, K, N, dtype, arity=[("gemm_ring", 15)])])[0]
+    kernels(answer)
+    rings = [la for la in answer["launches"] if "gemm_ring" in la["name"]]
+    assert all(la["status"] == 0 for la in answer["launches"])
+    at = 0
+    for la in rings:
+        assert la["ints"][14] == at
+        at += la["blocks"]
+    tiles_m, tiles_n, whole = rings[0]["ints"][10], rings[0]["ints"][11], rings[0]["ints"][13]
+    whole = min(whole, tiles_m * tiles_n)
+    assert at == whole + 4 * (tiles_m * tiles_n - whole)
