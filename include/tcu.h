@@ -271,7 +271,9 @@ int tcu_poly_eval_ex(const void *coef, int64_t n, const void *points, int64_t p,
  * every other block by the D function X_ij <- min(X_ij + X_ik X_kj, 1).
  * Pivot blocks here are 256 vertices wide, and while they are walked row i
  * of X holds its entries as bits in its first ceil(n/128)*16 bytes (n > 256):
- * other work must not read X until the call has finished on its stream.
+ * other work must not read X until the call has finished on its stream.  When a
+ * launch fails (TCU_ERR_HIP), X is still unpacked, to a graph between the given
+ * one and its closure, unless that launch fails too.
  * The unit size comes from tcu_get_unit() (it sets the cost accounting);
  * the stream from tcu_get_stream().  Errors: TCU_ERR_NULL, TCU_ERR_SHAPE
  * (n out of range, ld < n, extent of 2^40 bytes or more),

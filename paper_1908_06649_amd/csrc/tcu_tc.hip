@@ -364,6 +364,8 @@ hipError_t launch_tc(unsigned char *X, int64_t ld, int64_t n, hipStream_t stream
                      words);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  // From here on X holds bits: whatever fails, it is unpacked before the call
+  // returns (each step leaves a graph between the one given and its closure).
   hipLaunchKernelGGL(tc_diag_kernel, dim3(1), dim3(kThreads), 0, stream, X, ld);
   e = hipGetLastError();
   // A workgroup per CU (its tables fill the LDS), one of them for the next
@@ -384,10 +386,10 @@ hipError_t launch_tc(unsigned char *X, int64_t ld, int64_t n, hipStream_t stream
                        dim3(kThreads), 0, stream, X, ld, n, k0, Bk, quads, (int)slabs, share, next);
     e = hipGetLastError();
   }
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(tc_unpack_kernel, dim3(pack_grid), dim3(pack_threads), 0, stream, X, n, ld,
                      words);
-  return hipGetLastError();
+  const hipError_t unpacked = hipGetLastError();
+  return e != hipSuccess ? e : unpacked;
 }
 
 }  // namespace tcu

@@ -165,3 +165,20 @@ def test_largest_dimensions(so, M, K, N, dtype):
     tiles_m, tiles_n, whole = rings[0]["ints"][10], rings[0]["ints"][11], rings[0]["ints"][13]
     whole = min(whole, tiles_m * tiles_n)
     assert at == whole + 4 * (tiles_m * tiles_n - whole)
+
+
+@pytest.mark.parametrize("fail", [0, 1, 2, 4])
+def test_closure_unpacks_after_a_failed_launch(so, fail):
+    """Whichever launch fails, no more bands are walked and X does not stay
+    packed: the last launch turns it back into bytes."""
+    job = dict(fn="tcu_transitive_closure_ex", args=[rec.ptr(0), 1000, 1000, 16, None])
+    ok = rec.run(so, [job])[0]
+    names = kernels(ok)
+    assert [n.split("_kernel")[0] for n in names] == (
+        ["tc_pack", "tc_diag"] + ["tc_band"] * 4 + ["tc_unpack"])
+    bad = rec.run(so, [dict(job, fail=fail)])[0]
+    assert bad["rc"] == tcu.TCU_ERR_HIP
+    tried = [la["name"] for la in bad["launches"]]
+    assert [la["status"] != 0 for la in bad["launches"]].count(True) == 1
+    assert len(tried) == (1 if fail == 0 else fail + 2)
+    assert fail == 0 or "tc_unpack" in tried[-1]
