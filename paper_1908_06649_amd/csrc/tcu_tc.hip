@@ -231,7 +231,9 @@ __global__ __launch_bounds__(kThreads) void tc_band_kernel(unsigned char *__rest
   // tables of the slab, then of D* (narrow); block 0 keeps the next block's
   // narrow tables, its rows and the closure's data in the slab's place
   constexpr int kWideBytes = kGroups * 16 * 128;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kWideBytes + kNarrowBytes];
+  // (a group's 16 unions start at a multiple of 2048 bytes: their index is
+  // or-ed into the address)
+  __shared__ __attribute__((aligned(2048))) unsigned char smem[kWideBytes + kNarrowBytes];
   unsigned char *const tabX = smem, *const tabD = smem + kWideBytes;
   static_assert(kNarrowBytes + 256 * 32 + sizeof(DiagShared) <= kWideBytes, "block 0's LDS");
 
