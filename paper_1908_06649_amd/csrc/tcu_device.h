@@ -49,19 +49,15 @@ __device__ __forceinline__ f32x4 mfma_k32(int dt, u32x4 w, u32x4 x, f32x4 d) {
 }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef int i32x16 __attribute__((ext_vector_type(16)));
 
-// 32 x 32 output blocks: K = 16 (16-bit inputs) or 32 (int8) per
-// instruction, 16 bytes of operand per lane.  Lane l holds row (l % 32) of
+// 32 x 32 output blocks of 16-bit inputs: K = 16 per instruction, 16 bytes of
+// operand per lane.  Lane l holds row (l % 32) of
 // W and column (l % 32) of X over the contracted run selected by l / 32,
 // and D rows 8*(j/4) + 4*(l/32) + (j%4), j = 0..15, of column (l % 32).
 __device__ __forceinline__ f32x16 mfma32_k16(int dt, u32x4 w, u32x4 x, f32x16 d) {
   if (dt == TCU_F16_F32)
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(bitcast<f16x8>(w), bitcast<f16x8>(x), d, 0, 0, 0);
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(bitcast<bf16x8>(w), bitcast<bf16x8>(x), d, 0, 0, 0);
-}
-__device__ __forceinline__ i32x16 mfma32_i8_k32(u32x4 w, u32x4 x, i32x16 d) {
-  return __builtin_amdgcn_mfma_i32_32x32x32_i8(bitcast<i32x4>(w), bitcast<i32x4>(x), d, 0, 0, 0);
 }
 
 __device__ __forceinline__ i32x4 mfma_i8_k64(u32x4 w, u32x4 x, i32x4 d) {
@@ -130,14 +126,12 @@ __device__ __forceinline__ float bf16_to_f32(unsigned bits16) {
   return __builtin_bit_cast(float, bits16 << 16);
 }
 
-// One 16-byte chunk of EPC elements of ES bytes at p, of which the first
-// `valid` (0..EPC) lie inside the matrix; the others are returned as zero
-// (the zero padding of a partial strip or block) and are not read.  kVec:
-// p is 16-byte aligned, so a full chunk is one vector load.
-template <int ES, bool kVec>
+// One 16-byte chunk of EPC elements of ES bytes at p, element by element: the
+// first `valid` (0..EPC) lie inside the matrix; the others are returned as
+// zero (the zero padding of a partial strip or block) and are not read.
+template <int ES>
 __device__ __forceinline__ u32x4 load_chunk(const unsigned char *p, int valid) {
   constexpr int EPC = 16 / ES;
-  if (kVec && valid >= EPC) return *(const u32x4 *)p;
   u32x4 v = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (int e = 0; e < EPC; ++e) {

@@ -675,12 +675,12 @@ __device__ __forceinline__ void ring_tile(unsigned char *smem, const unsigned ch
     }
 #pragma unroll
     for (int i = 0; i < JA; ++i)
-      ra[i] = load_chunk<ES, false>(pa[i] + at,
+      ra[i] = load_chunk<ES>(pa[i] + at,
                                     max(min(kleft - a_chunk * EPC, EPC), 0));
 #pragma unroll
     for (int i = 0; i < JB; ++i) {
       const int nleft = N - n0 - b_chunk(w * JB + i) * EPC;
-      rb[i] = load_chunk<ES, false>(pb[i] + bt,
+      rb[i] = load_chunk<ES>(pb[i] + bt,
                                     b_row(w * JB + i) < kleft ? max(min(nleft, EPC), 0) : 0);
     }
   };

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kThreads) void poly_kernel(const unsigned char *__r
   constexpr int kStageBlocks = kStage / kBlockBytes / (kF16 ? 2 : 1);
   constexpr int kLo = kStageBlocks * kBlockBytes;
   auto chunk_at = [&](int row, int c) {   // row of a block, chunk c of its KP / 8
-    return row * (2 * KP) + 16 * (c ^ (KP == 64 ? row & 7 : KP == 32 ? (row >> 2) & 3 : (row >> 2) & 1));
+    return row * (2 * KP) + 16 * (c ^ ((row >> 2) & (KP / 8 - 1)));
   };
   auto fill_stage = [&](int64_t J0, int count) {   // blocks J0 .. J0 + count - 1
     for (int i = threadIdx.x; i < count * (kBlock / 8); i += kThreads) {
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kThreads) void poly_kernel(const unsigned char *__r
       const int64_t left = n - at;
       const unsigned char *src = coef + 2 * at;
       u32x4 v = left >= 8 ? *(const u32x4 *)src
-                          : load_chunk<2, false>(src, left > 0 ? (int)left : 0);
+                          : load_chunk<2>(src, left > 0 ? (int)left : 0);
       const int blk = i / (kBlock / 8), in = i % (kBlock / 8);
       unsigned char *dst = stage + blk * kBlockBytes + chunk_at(in / (KP / 8), in % (KP / 8));
       if constexpr (kF16) {
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kThreads) void poly_kernel(const unsigned char *__r
       // so that it cannot overflow where the polynomial does not: every
       // power kept divides x^(n-1).
       const float x32 = x16 * x16;
-      const float y = KP == 64 ? x32 * x32 : KP == 32 ? x32 : x16;
+      const float y = KP == 32 ? x32 : x16;
       const float y2 = y * y, y4 = y2 * y2, y8 = y4 * y4, y16 = y8 * y8;
       yv[u] = ncols >= 2 ? y : 0.f;
       y8v[u] = ncols > 8 ? y8 : 0.f;

@@ -71,7 +71,7 @@ __device__ __forceinline__ unsigned bits4_to_bytes(unsigned b) {
 __device__ __forceinline__ u32x4 row_chunk(const unsigned char *row, int64_t c, int64_t n) {
   if (c + 16 <= n) return load16_any(row + c);
   if (c >= n) return u32x4{0u, 0u, 0u, 0u};
-  if (n < 16) return load_chunk<1, false>(row + c, (int)(n - c));
+  if (n < 16) return load_chunk<1>(row + c, (int)(n - c));
   return shift_down(load16_any(row + n - 16), (int)(c - (n - 16)));
 }
 // Word w of a row: the edges to vertices 32 w .. 32 w + 31.
