@@ -409,7 +409,7 @@ TCU_EXPORT int tcu_poly_eval_ex(const void *coef, int64_t n, const void *points,
   if (rc != TCU_OK) return rc;
   rc = check_ranges({{coef, n * 2}, {points, p * 2}, {out, p * out_size(dtype)}});
   if (rc != TCU_OK) return rc;
-  if (tcu::launch_poly(dtype, coef, n, points, p, out, (hipStream_t)hip_stream, num_cus) !=
+  if (tcu::launch_poly(dtype, s, coef, n, points, p, out, (hipStream_t)hip_stream, num_cus) !=
       hipSuccess)
     return TCU_ERR_HIP;
   // Theorem 11: ceil(n/m) calls of X (p x s) times an s x s coefficient

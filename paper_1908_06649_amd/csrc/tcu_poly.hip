@@ -7,8 +7,7 @@
 //     entry (k, j) = a_(k + j KP);
 //   * C = X times that matrix;
 //   * A(x_i) = sum_j C[i][j] x_i^(j KP).
-// KP is 16 or 32, by the length of the polynomial; the unit size s only sets
-// the cost accounting, as it does for the fused product.
+// KP is 16 or 32: the unit size s, or 16 for a short polynomial.
 // Each wave owns chunks of 32 points, one point per matrix-core column:
 //   * it computes the powers of its points in binary32 (the theorem's
 //     initial exponentiation, as a ladder of squarings shared by all lanes
@@ -326,38 +325,47 @@ hipError_t launch_poly_cfg(const void *coef, int64_t n, const void *pts, int64_t
 }
 
 // The shape by size (us for 2^24 points, n = 100 and 1000; 2^22, n = 65536; bf16):
-//   * up to 1024 coefficients, 16 powers per column: the powers and their split
-//     are most of the work (KP = 16: 89, 127; KP = 32: 128, 136), above that
-//     32, which halves the combine (n = 4096, 2^24 points: 336 / 275; 64 powers: 315);
+//   * powers per column: with s = 32 and more than 1024 coefficients 32, which
+//     halves the combine (n = 4096, 2^24 points: 336 / 275; 64 powers: 315); up to
+//     1024 the powers and their split are most of the work and 16 are faster (KP = 16:
+//     89, 127; KP = 32: 128, 136).  With s = 16 always 16, the s of the method: its
+//     columns hold fewer powers that the split rounds (x^0 to x^2 are exact in
+//     bfloat16 hi + lo), and 32 raised the error's norm by 6 to 22 % (n = 1025 to 20000);
 //   * coefficients beyond a 32 KiB stage: one workgroup of 16 waves around
 //     128 KiB, so that up to 2^16 bfloat16 coefficients are loaded once (n = 65536:
 //     858 with the small stage refilled on every pass);
 //   * too few points to give every SIMD a wave of two chunks: one chunk per
 //     wave (n = 65536, 1000 points: 20.9 -> 15.7).
-template <int DT>
-hipError_t launch_poly_dt(const void *coef, int64_t n, const void *pts, int64_t np, void *out,
+template <int DT, int KP>
+hipError_t launch_poly_kp(const void *coef, int64_t n, const void *pts, int64_t np, void *out,
                           hipStream_t stream, int num_cus) {
   constexpr int kSmall = 32768, kBig = 131072;
   const int64_t waves = (np + 63) / 64;   // with two chunks each
-  const bool few = waves < 4 * (int64_t)num_cus;
-  if (n <= 1024)
-    return few ? launch_poly_cfg<DT, 16, 1, 256, kSmall>(coef, n, pts, np, out, stream, num_cus)
-               : launch_poly_cfg<DT, 16, 2, 256, kSmall>(coef, n, pts, np, out, stream, num_cus);
-  if (few) return launch_poly_cfg<DT, 32, 1, 256, kSmall>(coef, n, pts, np, out, stream, num_cus);
+  if (waves < 4 * (int64_t)num_cus)
+    return launch_poly_cfg<DT, KP, 1, 256, kSmall>(coef, n, pts, np, out, stream, num_cus);
   const int64_t bytes = n * (DT == TCU_F16_F32 ? 4 : 2);   // binary16 is stored split
   if (bytes > kSmall && waves >= 16 * (int64_t)num_cus)
-    return launch_poly_cfg<DT, 32, 2, 1024, kBig>(coef, n, pts, np, out, stream, num_cus);
-  return launch_poly_cfg<DT, 32, 2, 256, kSmall>(coef, n, pts, np, out, stream, num_cus);
+    return launch_poly_cfg<DT, KP, 2, 1024, kBig>(coef, n, pts, np, out, stream, num_cus);
+  return launch_poly_cfg<DT, KP, 2, 256, kSmall>(coef, n, pts, np, out, stream, num_cus);
+}
+template <int DT>
+hipError_t launch_poly_dt(int s, const void *coef, int64_t n, const void *pts, int64_t np,
+                          void *out, hipStream_t stream, int num_cus) {
+  if (s == 16 || n <= 1024)
+    return launch_poly_kp<DT, 16>(coef, n, pts, np, out, stream, num_cus);
+  return launch_poly_kp<DT, 32>(coef, n, pts, np, out, stream, num_cus);
 }
 
 }  // namespace
 
-hipError_t launch_poly(int dtype, const void *coef, int64_t n, const void *pts, int64_t np,
+hipError_t launch_poly(int dtype, int s, const void *coef, int64_t n, const void *pts, int64_t np,
                        void *out, hipStream_t stream, int num_cus) {
   switch (dtype) {
-    case TCU_F16_F32: return launch_poly_dt<TCU_F16_F32>(coef, n, pts, np, out, stream, num_cus);
-    case TCU_BF16_F32: return launch_poly_dt<TCU_BF16_F32>(coef, n, pts, np, out, stream, num_cus);
-    case TCU_BF16_BF16: return launch_poly_dt<TCU_BF16_BF16>(coef, n, pts, np, out, stream, num_cus);
+    case TCU_F16_F32: return launch_poly_dt<TCU_F16_F32>(s, coef, n, pts, np, out, stream, num_cus);
+    case TCU_BF16_F32:
+      return launch_poly_dt<TCU_BF16_F32>(s, coef, n, pts, np, out, stream, num_cus);
+    case TCU_BF16_BF16:
+      return launch_poly_dt<TCU_BF16_BF16>(s, coef, n, pts, np, out, stream, num_cus);
   }
   return hipErrorInvalidValue;
 }

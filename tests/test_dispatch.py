@@ -182,3 +182,13 @@ def test_closure_unpacks_after_a_failed_launch(so, fail):
     assert [la["status"] != 0 for la in bad["launches"]].count(True) == 1
     assert len(tried) == (1 if fail == 0 else fail + 2)
     assert fail == 0 or "tc_unpack" in tried[-1]
+
+
+@pytest.mark.parametrize("n,p,s,powers", [(1000, 1 << 20, 16, 16), (1000, 1 << 20, 32, 16),
+                                          (1025, 1 << 20, 16, 16), (1025, 1 << 20, 32, 32),
+                                          (20000, 1 << 20, 16, 16), (20000, 1 << 20, 32, 32),
+                                          (5000, 100, 16, 16), (5000, 100, 32, 32)])
+def test_poly_powers_per_column(so, n, p, s, powers):
+    """With s = 16 a column never holds more than 16 powers (32 cost precision)."""
+    job = dict(fn="tcu_poly_eval_ex", args=[rec.ptr(0), n, rec.ptr(1), p, rec.ptr(2), s, BF16, None])
+    assert kernels(rec.run(so, [job])[0])[0].startswith(f"poly_kernelILi{BF16}ELi{powers}E")
