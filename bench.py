@@ -27,9 +27,9 @@ JSON line:
              levels, or two consecutive levels fused through LDS -- reads and
              writes the array once) vs HBM peak, and 5 n log2 n GFLOP/s
   tc         transitive closure (tcu_transitive_closure, Theorem 5) of a
-             random 8192-vertex digraph: GB/s of the D updates' algorithmic
-             traffic (each pivot band reads and writes the off-band n^2 bytes)
-             vs HBM peak, and boolean TOP/s (2 n^3 / t); every timed call
+             random 8192-vertex digraph: GB/s of the traffic of its passes (the
+             bytes once in and out, and the matrix as bits read and written by
+             every pivot band) vs HBM peak, and boolean TOP/s (2 n^3 / t); every timed call
              starts from the raw graph (restored outside the timed region);
              the oracle's closure timed and compared exactly
   rect       the rectangular / accumulating product (tcu_gemm_rect):
@@ -125,10 +125,11 @@ def dft_levels(n: int, s: int) -> int:
 
 def dft_launches(n: int, s: int) -> int:
     """Launches of tcu_dft for a vector too long to be transformed whole in LDS
-    (n > 2^13; shorter ones take one): two consecutive full-radix levels in
-    one launch where the library pairs them (level t+1 of full radix, and
-    P_t >= 16 or P_t = 1 with at least 16 groups per vector), else one
-    launch per level.  Each launch reads and writes the array once."""
+    (n > 2^13; shorter ones take one, but for few of 2^12 and 2^13 with s = 16):
+    two consecutive full-radix levels in one launch where the library pairs
+    them (level t+1 of full radix, and P_t >= 16 or P_t = 1 with at least 16
+    groups per vector), else one launch per level.  Each launch reads and
+    writes the array once."""
     levels, P, t, launches = dft_levels(n, s), 1, 1, 0
     while t <= levels:
         n2 = n // P // s
@@ -150,14 +151,12 @@ def algorithmic(spec: dict):
         n, b = spec["n"], spec["batch"]
         return 5.0 * b * n * math.log2(n), dft_launches(n, spec["s"]) * 2 * 8 * b * n
     if spec["kind"] == "tc":
-        # per pivot band of up to 256 vertices: the D update reads and writes
-        # every off-band entry once, the panel updates their band entries
+        # the matrix read and written once as bytes; beyond one band of 256
+        # vertices it is held as bits meanwhile: written when packed, read when
+        # unpacked, and read and written by the update of every pivot band
         n = spec["n"]
-        nbytes = 0
-        for k0 in range(0, n, 256):
-            bk = min(256, n - k0)
-            nbytes += 2 * (n - bk) ** 2 + 2 * 2 * bk * (n - bk) + 2 * bk * bk
-        return 2.0 * n ** 3, nbytes + 2 * n * n          # + the normalizing pass
+        packed = n * -(-n // 128) * 16
+        return 2.0 * n ** 3, 2 * n * n + (2 * packed * (1 + -(-n // 256)) if n > 256 else 0)
     if spec["kind"] == "poly":
         n, p = spec["n"], spec["p"]
         return 2.0 * n * p, n * ib + p * ib + p * ob

@@ -1203,7 +1203,7 @@ GemmPath gemm_path() {
 // the smaller tiles, which fetch whole lines, more than the full ones.
 // Filled through registers the ring kernel takes 1.1 to 1.25 times as long.
 // Split ranges are added atomically, after zeroing C when overwriting:
-// f16 192 x 8192 x 320 (15 tiles of 64) 37 us whole, 10.4 with 16 ranges,
+// f16 192 x 8192 x 320 (15 tiles of 64) 37 us whole, 10.1 with 18 ranges,
 // 12.9 with 32; bf16 N = 3072 full-tile 74 whole, 135 with 2 ranges.
 // ---------------------------------------------------------------------------
 enum class Tile { kFull, k128, k64, kWave32, kWave16 };

@@ -40,10 +40,13 @@ def test_algorithmic_rect_poly_tc_dft():
     n, p = 4096, 1 << 24
     w, b = bench.algorithmic(inputs.POLY_WORKLOADS["poly_bf16_n4096_p16777216_s32"])
     assert w == 2 * n * p and b == 2 * n + 2 * p + 4 * p
-    # one pivot band (n <= 256): the diagonal block read and written, plus
-    # the normalizing pass
+    # one pivot band (n <= 256): the bytes read and written once; 1000
+    # vertices: rows of 128 bytes as bits, written by the packing, read by the
+    # unpacking and both by each of the four bands
     w, b = bench.algorithmic({"kind": "tc", "n": 256})
-    assert w == 2 * 256 ** 3 and b == 2 * 256 * 256 + 2 * 256 * 256
+    assert w == 2 * 256 ** 3 and b == 2 * 256 * 256
+    w, b = bench.algorithmic({"kind": "tc", "n": 1000})
+    assert w == 2 * 1000 ** 3 and b == 2 * 1000 ** 2 + 2 * 5 * 1000 * 128
     # DFT: the 4 radix-32 levels of 2^20 run as 2 launches (levels 1-2 and
     # 3-4 fused), each reading and writing the array once
     w, b = bench.algorithmic(inputs.DFT_WORKLOADS["dft_c64_n1048576_b16_s32"])

@@ -124,9 +124,8 @@ def test_workload_i8_N8192_s32_all_rows():
 
 
 # Every kernel of the product on sizes where it applies (N % 256 == 0): the
-# full-tile kernel (DMA-fed LDS ring, transposing reads), the general one
-# (register-staged, predicated tails) and the small-tile ring kernel (16-bit
-# inputs; int8 falls back to the general kernel under "ring").
+# full-tile kernel (DMA-fed LDS ring, transposing reads) and the ring kernel filled
+# through registers ("general") or by DMA on its 64 x 64 tiles ("ring").
 @pytest.mark.parametrize("path", ["fast", "general", "ring"])
 @pytest.mark.parametrize("din,dout", DTYPES)
 @pytest.mark.parametrize("N,s", [(256, 16), (512, 32), (1280, 32)])

@@ -66,7 +66,7 @@ def test_rect_ragged(M, K, N, din, out, accumulate, pitch):
 
 
 # Whole 256 x 256 tiles and whole K stages: the full-tile kernel, forced, on
-# rectangular shapes with padded pitches, against the general kernel.
+# rectangular shapes with padded pitches, and the ring kernel through registers.
 FULL = [(256, 32, 256), (256, 64, 512), (512, 1024, 768), (768, 2048, 256)]
 
 
@@ -81,9 +81,9 @@ def test_rect_full_tiles(M, K, N, din, out, accumulate, kernel, knobs):
     run_and_check(M, K, N, din, out, 32, "padded", accumulate, seed=M + K + N)
 
 
-# Whole 64 x 64 tiles and 128-byte K stages with 16-bit inputs: the
-# small-tile ring kernel, forced, from one tile and one stage to long K
-# (many refills of its 8-slot ring) and to more tiles than CUs.
+# Whole 64 x 64 tiles and 128-byte K stages with 16-bit inputs: the ring
+# kernel's 64 x 64 tiles, forced, from one tile and one stage to long K (many
+# refills of its slots) and to more tiles than CUs.
 RING = [(64, 64, 64), (64, 128, 192), (192, 448, 128), (320, 960, 128), (128, 4096, 64),
         (1024, 1024, 1024), (2048, 192, 2112)]
 
