@@ -366,16 +366,21 @@ struct LevelIndex {
 
 // One level.  n, R, P, N_t are powers of two and enter as their base-2
 // logarithms; ntrans = batch * n / R transforms, 16 S/R per wave step.
-// R < S only on the last level.
+// R < S (kNarrow) only on the last level, which scales nothing: its kernel holds no
+// table and no code for one (n = 2^14, s = 32, 32 MiB: 194 -> 161 registers, two ->
+// three waves per SIMD; with the grid of launch_level 17.8 -> 12.1 us).
 template <int S, bool kNarrow>
 __global__ __launch_bounds__(kDftThreads) void dft_level_kernel(
     const f32x2 *__restrict__ src, f32x2 *__restrict__ dst, int lg_n, int lg_r, int lg_p,
-    int64_t ntrans, int scale, int lg_p0) {
+    int64_t ntrans, int scale_, int lg_p0) {
   constexpr int kRun = DftShape<S>::kRun, kH = DftShape<S>::kH;
   constexpr int lg_s = DftScale<S>::lg_s;
   __shared__ f32x2 wtab[S];               // w_R^m, m < R
-  __shared__ __attribute__((aligned(16))) f32x2 vtab[S * S];
-  __shared__ f32x2 pool[tab_entries(kTabLg)];
+  // the one table that `scale` asks for: of a pair's first twiddles, or of N_t
+  constexpr int kPool = kNarrow ? 1 : tab_entries(kTabLg);
+  static_assert(kNarrow || kPool >= S * S, "the pair table fits");
+  __shared__ __attribute__((aligned(16))) f32x2 pool[kPool];
+  const int scale = kNarrow ? kNone : scale_;
 
   const int R = 1 << lg_r;
   const int lg_nt = lg_n - lg_p;          // log2 N_t
@@ -387,8 +392,8 @@ __global__ __launch_bounds__(kDftThreads) void dft_level_kernel(
   sf.scale = scale;
   sf.lg_jp = lg_nt - 2 * lg_s;
   sf.lg_p0 = lg_p0;
-  sf.pair = vtab;
-  if (scale == kPairFirst) build_pair_tab<S>(vtab, threadIdx.x, kDftThreads);
+  sf.pair = pool;
+  if (scale == kPairFirst) build_pair_tab<S>(pool, threadIdx.x, kDftThreads);
   if (scale == kOwn || scale == kPairSecond)
     sf.tab = build_tab(pool, DftScale<S>::tab_lg(scale, lg_nt), threadIdx.x, kDftThreads);
   __syncthreads();
@@ -848,7 +853,14 @@ hipError_t launch_level(const f32x2 *src, f32x2 *dst, int64_t n, int R, int64_t 
   const int64_t per_chunk = 16 * S / R;
   const int64_t nchunks = (ntrans + per_chunk - 1) / per_chunk;
   const int64_t want = (nchunks + 3) / 4;
-  const int64_t cap = (int64_t)num_cus * 8;
+  // A narrow level's workgroups are bound by its two passes over memory and hold
+  // three per CU (s = 32): with that many the weights are formed once, 12 per CU
+  // are faster when the array no longer stays in the memory-side cache (us, 3 / 8 / 12
+  // per CU, whole transforms of n = 2^14, s = 32: 24 MiB 23.8 / 25.2 / 25.4, 32 MiB
+  // 29.0 / 30.6 / 30.8, 64 MiB 53.1 / 53.2 / 54.2, 256 MiB 219 / 222 / 217; n = 2^18,
+  // 256 MiB 320 / 314 / 307).
+  const int64_t per_cu = R == S ? 8 : batch * n * 8 <= (int64_t)64 << 20 ? 3 : 12;
+  const int64_t cap = num_cus * per_cu;
   const int blocks = (int)(want < cap ? want : cap);
   const int lg_p0 = scale == kPairSecond ? ilog2(P / S) : 0;
   if (R < S)

@@ -61,6 +61,18 @@ def test_dft_division(so, n, batch, s, launches):
     assert (launches == 1) == names[0].startswith("dft_local")
 
 
+# The last level of radix below s: three workgroups per compute unit, 12 for arrays
+# of more than 64 MiB; a workgroup of four waves takes 64 s elements.
+@pytest.mark.parametrize("n,batch,s,blocks", [
+    (1 << 14, 4, 32, 32), (1 << 14, 97, 32, 768), (1 << 14, 512, 32, 768),
+    (1 << 14, 513, 32, 3072), (1 << 14, 200, 16, 768), (1 << 14, 1024, 16, 3072)])
+def test_dft_narrow_grid(so, n, batch, s, blocks):
+    job = dict(fn="tcu_dft_ex", args=[rec.ptr(0), rec.ptr(1), rec.ptr(2), n, batch, s, None])
+    answer = rec.run(so, [job])[0]
+    assert kernels(answer)[-1] == f"dft_level_kernelILi{s}ELb1E"
+    assert answer["launches"][-1]["blocks"] == blocks
+
+
 def aligned(cols, dtype_bytes, extra):
     """The padded pitches of the GPU tests."""
     step = 16 // dtype_bytes
