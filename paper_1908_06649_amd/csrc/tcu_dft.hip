@@ -824,9 +824,20 @@ hipError_t launch_pair(const f32x2 *src, f32x2 *dst, int64_t n, int64_t P, int64
   // The caller's input (P = 1) of an array that the memory-side cache cannot
   // hold beside the other two is read past the caches, so that it does not
   // push out what the next launch reads: n = 2^20, batch 16 (128 MiB) 127 ->
-  // 118 us, n = 2^16, batch 256, s = 16 128 -> 114 us; n = 2^20, batch 2 (16
-  // MiB) loses, 23.2 -> 24.9 us, batch 4 gains, 34.1 -> 31.1.
-  const bool stream_in = batch * n * 8 >= (int64_t)32 << 20;
+  // 118 us, n = 2^16, batch 256, s = 16 128 -> 114 us.  Below that it depends on
+  // the input (us, plain / past the caches; in the cache from the call before, from a
+  // kernel that wrote it just before, or in neither):
+  //   s = 16, n = 2^20, 32 MiB 48.3 / 51.3, 60.4 / 63.4, 50.0 / 51.4;
+  //                     64 MiB 84.9 / 91.3, 108 / 112, 90.9 / 92.1;
+  //           n = 2^14, 64 MiB 73.0 / 77.9, 94.9 / 99.4, 83.0 / 80.0;
+  //           n = 2^16, 96 MiB 85.5 / 81.6, 111 / 111, 87.4 / 85.3;
+  //   s = 32, n = 2^20, 32 MiB 29.6 / 35.1, 42.5 / 44.7, 35.9 / 35.1;
+  //                     64 MiB 54.9 / 59.3, 78.4 / 81.7, 60.7 / 57.9;
+  //           n = 2^14, 32 MiB 30.1 / 30.6, 42.1 / 43.2, 36.3 / 30.7.
+  // So s = 16 reads it plainly up to 64 MiB; s = 32, whose shorter launches lose
+  // more on an input that is in no cache, below 32 (n = 2^20, 16 MiB 23.2 / 24.9).
+  const bool stream_in = S == 32 ? batch * n * 8 >= (int64_t)32 << 20
+                             : batch * n * 8 > (int64_t)64 << 20;
   // Later pairs read the other buffer for the last time, past the caches from
   // 64 MiB on: its lines then make room for the output's.  n = 2^20, batch 16
   // 113.1 -> 110.2 us, batch 8 58.7 -> 57.2; batch 4 (32 MiB) 30.8 both.

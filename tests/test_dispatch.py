@@ -61,6 +61,16 @@ def test_dft_division(so, n, batch, s, launches):
     assert (launches == 1) == names[0].startswith("dft_local")
 
 
+# The first pair reads its input past the caches from 32 MiB on with s = 32, past 64
+# MiB with s = 16.
+@pytest.mark.parametrize("n,batch,s,past", [
+    (1 << 20, 3, 32, 0), (1 << 20, 4, 32, 1), (1 << 20, 8, 16, 0), (1 << 20, 9, 16, 1),
+    (1 << 14, 512, 16, 0), (1 << 14, 513, 16, 1)])
+def test_dft_input_past_caches(so, n, batch, s, past):
+    job = dict(fn="tcu_dft_ex", args=[rec.ptr(0), rec.ptr(1), rec.ptr(2), n, batch, s, None])
+    assert kernels(rec.run(so, [job])[0])[0] == f"dft_pair_kernelILi{s}ELb0ELb{past}E"
+
+
 # The last level of radix below s: three workgroups per compute unit, 12 for arrays
 # of more than 64 MiB; a workgroup of four waves takes 64 s elements.
 @pytest.mark.parametrize("n,batch,s,blocks", [
