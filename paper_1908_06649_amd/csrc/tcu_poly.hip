@@ -330,7 +330,9 @@ hipError_t launch_poly_cfg(const void *coef, int64_t n, const void *pts, int64_t
 //     1024 the powers and their split are most of the work and 16 are faster (KP = 16:
 //     89, 127; KP = 32: 128, 136).  With s = 16 always 16, the s of the method: its
 //     columns hold fewer powers that the split rounds (x^0 to x^2 are exact in
-//     bfloat16 hi + lo), and 32 raised the error's norm by 6 to 22 % (n = 1025 to 20000);
+//     bfloat16 hi + lo), and 32 raised the error's norm by 6 to 22 % (n = 1025 to 20000).
+//     The price of 16 at s = 16 (us, 16 / 32): n = 20000, 30000 points 8.9 / 6.9; n = 65536,
+//     131072 points 35.4 / 30.7; n = 2^20, 1000 points, a long chain per wave, 331 / 207;
 //   * coefficients beyond a 32 KiB stage: one workgroup of 16 waves around
 //     128 KiB, so that up to 2^16 bfloat16 coefficients are loaded once (n = 65536:
 //     858 with the small stage refilled on every pass);
